@@ -260,6 +260,7 @@ SweepArgs<R> make_args(const ep_handle* h, R* const* from, R* const* to, R* cons
         for (int f = 0; f < O_N; ++f) ok = ok && old[f] == old[0] + f * fs;
         if (ok) a.fs = fs;
     }
+    a.plan = h->plan[sizeof(R) == 4][h->has_g];
     return a;
 }
 
@@ -300,7 +301,7 @@ void launch_sweep(const ep_handle* h, bool physical, int from, int mode, int lam
     if (h->ndim == 2) {
         launch_sweep_unfused_2d<R>(a, mode, h->st);
     } else {
-        if (fused && a.fs > 0) launch_sweep_fused_3d<R>(a, mode, h->st);
+        if (fused && a.fs > 0 && a.plan.zc > 0) launch_sweep_fused_3d<R>(a, mode, h->st);
         else launch_sweep_unfused_3d<R>(a, mode, h->st);
     }
 }
@@ -831,6 +832,8 @@ int handle_create(const ep_params* p, const double* cohesion, char* d_workspace,
     // MI355X; FUSED / UNFUSED force one for both precisions
     h->fused32 = p->sweep == EP_SWEEP_FUSED || (p->sweep == EP_SWEEP_AUTO && fused_preferred(p->ndim, true));
     h->fused64 = p->sweep == EP_SWEEP_FUSED || (p->sweep == EP_SWEEP_AUTO && fused_preferred(p->ndim, false));
+    for (int q = 0; q < 4 && h->ndim == 3; ++q)
+        h->plan[q >> 1][q & 1] = fused_plan_3d((q >> 1) != 0, (q & 1) != 0, h->nx, h->ny, h->nz, h->sz);
     h->cur64 = 0;
     h->cur32 = 0;
     auto fail = [&](int code) { delete h; return code; };
@@ -1068,7 +1071,7 @@ int ep_residual_noalloc(ep_handle* h, ep_residual_info* r)
             launch_sweep_batch_2d<double>(SINGLE_SHAPE, tab + q, tiles, cnt, mode, h->grid2[0], h->st);
         else if (h->ndim == 2)
             launch_sweep_unfused_2d<double>(a[q], mode, h->st);
-        else if (h->fused64 && a[q].fs > 0)
+        else if (h->fused64 && a[q].fs > 0 && a[q].plan.zc > 0)
             launch_sweep_fused_3d<double>(a[q], mode, h->st);
         else
             launch_sweep_unfused_3d<double>(a[q], mode, h->st);

@@ -38,6 +38,7 @@ struct ep_handle {
     double dx, dy, dz, eta, gdtau, kdtau, dtrho, A, B, C, L, h, inv_mus, dsig_ref;
     int n_check;
     bool fp32, fused32, fused64;
+    ep::FusedPlan plan[2][2];   // 3D fused sweep: [FP64, FP32][uniform, per-cell G]
     double* it64[2][ep::F_NIT];
     int cur64;
     double* old64[ep::O_N];

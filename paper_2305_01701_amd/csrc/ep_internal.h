@@ -21,6 +21,12 @@ enum { O_P = 0, O_TXX, O_TYY, O_TXY, O_TXZ, O_TYZ, O_N };
 // integer atomicMax; NaN is mapped to +inf before reduction).
 enum { RED_RESID = 0, RED_MOM, RED_VMAX, RED_NYIELD, RED_VIOL, RED_SMAX, RED_CONT, RED_N = 8 };
 
+// Tile (TILE_* of the fused sweep) and planes per z chunk of a fused 3D
+// sweep; zc = 0: the grid is out of the kernel's range.
+struct FusedPlan {
+    int tile, zc;
+};
+
 // Scalars of one PT sweep.  Kernel arguments by value.
 template <typename R>
 struct SweepArgs {
@@ -54,6 +60,7 @@ struct SweepArgs {
     int lam_mode;          // 2D tile sweep: LAM_* (frozen plasticity)
     long fs;               // 3D: element stride between consecutive fields of it, nx_ and old
                            // (field f of a group = group[0] + f * fs; 0 when not uniform)
+    FusedPlan plan;        // 3D: how the fused sweep splits the grid
 };
 
 // Centre Lambda of the 2D tile sweep: from the return mapping; from the
@@ -71,6 +78,9 @@ enum { MODE_UPDATE = 0,    // write iteration k+1
 template <typename R> void launch_sweep_unfused_2d(const SweepArgs<R>& a, int mode, hipStream_t s);
 template <typename R> void launch_sweep_unfused_3d(const SweepArgs<R>& a, int mode, hipStream_t s);
 template <typename R> void launch_sweep_fused_3d(const SweepArgs<R>& a, int mode, hipStream_t s);
+// Split of the fused 3D sweep for a grid of nx x ny x nz cells with padded
+// planes of sz elements.
+FusedPlan fused_plan_3d(bool fp32, bool has_g, int nx, int ny, int nz, long sz);
 // Whether the automatic choice uses the fused sweep for this case.
 bool fused_preferred(int ndim, bool fp32);
 

@@ -4,24 +4,32 @@
 // edges -> 4-point mean at centres -> Lambda at centres -> mean back to
 // edges -> velocity), so a workgroup that owns a tile recomputes a halo:
 //
-//   3D: a workgroup owns a TX x TY column of cells over a chunk of ZC
-//   z-planes and marches up the chunk.  Every quantity lives in LDS as 2D
-//   planes of (TX+4) x (TY+4) points (a 2-point x-y halo) in two-slot ring
-//   buffers over z.  Step f of the march forms the shear trials on the
-//   z-level f (xz, yz edges) and the plane f-1 (xy edges), the centre update
-//   of plane f-1 (pressure, deviator, return mapping), the new edge stresses
-//   of plane/level f-1, and the new velocities of plane f-2 (vx, vy) and
-//   level f-1 (vz), then stores the velocity planes of step f+1 to LDS: four
-//   workgroup barriers per step.  The velocity stage updates each thread's
-//   own plane points, whose old values the thread keeps in registers.  Each
-//   field is read from and written to HBM once per sweep; the halo reads of
-//   neighbouring tiles are served by L2 (blocks are remapped so that spatial
-//   neighbours run on the same XCD).
+//   3D: a workgroup owns a TX x TY column of cells over a chunk of z-planes
+//   and marches up the chunk.  What neighbours exchange lives in LDS as 2D
+//   planes of (TX+4) x (TY+4) points (a 2-point x-y halo).  Step f of the
+//   march forms the shear trials on the z-level f (xz, yz edges) and the
+//   plane f-1 (xy edges), the centre update of plane f-1 (pressure, deviator,
+//   return mapping), the new edge stresses of plane/level f-1, and the new
+//   velocities of plane f-2 (vx, vy) and level f-1 (vz), then stores the
+//   velocity planes of step f+1 to LDS: four workgroup barriers per step.
+//   Each field is read from and written to HBM once per sweep (iteration-k
+//   velocities twice, from L2); the halo reads of neighbouring tiles are
+//   served by L2 (blocks are remapped so that spatial neighbours run on the
+//   same XCD).
+//   What bounds it: large grids the memory traffic (255^3 FP32: 2.7 GB per
+//   sweep with 32 x 16 tiles, 5.4 TB/s), small ones the latency of a march
+//   step.  An earlier form kept every plane twice in LDS, split the points
+//   over the threads once for all stages and loaded behind branches: 80
+//   vector registers with spills, whose reloads waited for the loads of the
+//   next step.  Per sweep, then and now, in us: 255^3 FP32 541 and 464, FP64
+//   989 and 811; 190 x 127 x 101 FP64 247 and 155; 63^3 FP32 142 and 18.5,
+//   FP64 194 and 25 (short chunks included).
 //   2D: the same stages on a single TX x TY tile (ep_tile2d.h, run by the
 //   tile-list kernel of ep_sweep_batch.hip for single models and batches).
 //
 // The arithmetic of every point is that of the unfused sweep (same formulas,
 // same Jacobi order: all reads are of iteration k, all writes iteration k+1).
+#include <cmath>
 #include <type_traits>
 
 #include "ep_device.h"
@@ -30,41 +38,79 @@ namespace ep {
 
 namespace {
 
-__device__ __forceinline__ int mod2(int f) { return f & 1; }
-
 // Tile grid of a 3D sweep and its interior rectangle [bx0, bx1) x [by0,
 // by1): tiles whose points, 2-point halo included, lie strictly inside the
 // domain in x and y.
 struct TileSet {
-    int nbx, nby, nbz;
+    int nbx, nby, nbz, zc;      // tiles per direction, planes per z chunk
     int bx0, bx1, by0, by1;
 };
 
+// Global memory is reached through buffer instructions: a field of the
+// chunk is a resource (base of its first plane, 2 GiB range), a point a
+// 32-bit in-plane offset per lane plus a uniform plane offset.  A lane that
+// must not access memory carries the offset NOWHERE, which the range check
+// turns into a load of 0 or a dropped store, and a store that a whole step
+// must not do gets an empty range.  So every load and store is issued
+// unconditionally, and the compiler knows how many memory operations are in
+// flight when it waits for one (behind a branch it would have to assume the
+// fewest, and wait for younger ones too).
+constexpr unsigned NOWHERE = 0xffffffffu;
+constexpr int RANGE = 0x7fffffff;
+
+template <typename R>
+__device__ __forceinline__ R buf_load(const char* base, bool go, unsigned off, int plane)
+{
+    const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, go ? RANGE : 0, 0x00020000);
+    if constexpr (sizeof(R) == 4) return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b32(rs, off, plane, 0));
+    else return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b64(rs, off, plane, 0));
+}
+
+template <typename R>
+__device__ __forceinline__ void buf_store(char* base, bool go, unsigned off, int plane, R v)
+{
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, go ? RANGE : 0, 0x00020000);
+    if constexpr (sizeof(R) == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rs, off, plane, 0);
+    else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), rs, off, plane, 0);
+}
+
+// The value as it is, hidden from the compiler: an expression of it is not
+// fused with the one that formed it.
+template <typename R>
+__device__ __forceinline__ R opaque(R v) { asm volatile("" : "+v"(v)); return v; }
+
+// LDS planes.  Velocities, xz / yz trials and compliances come in pairs
+// (planes of even and of odd z): slot 0 of all of them, then slot 1, so that
+// one address per slot and an immediate offset reach every plane of a point.
+// Of the rest one plane is kept: what a thread needs of the plane below it
+// carries over in registers (sums and differences are formed in the order in
+// which the two planes come by).
+enum { L_VX = 0, L_VY, L_VZ, L_SXZ, L_SYZ, L_PAIRS, L_IG = L_PAIRS };
+enum { L_SXY = 0, L_LAM, L_XX, L_YY, L_ZZ, L_NXY, L_NXZ, L_NYZ, L_SINGLE };
+
 // ----------------------------------------------------------------------- 3D
-// Global data a march step needs is prefetched into registers one step
-// ahead (velocities of plane f+1, edge stresses of level f+1 and plane f,
-// centre data of plane f, and with a per-cell G the compliances of plane
-// f+1), so that HBM latency overlaps the LDS work of the current step.  Each
-// thread owns the same plane positions in every step; the edge stage (S4)
-// works on the edge points among them, so the edge stresses of iteration k
-// it needs (for the pseudo-time trial and the residual) are the thread's own
-// prefetched values, and only the physical trials S (which the centres
-// average) go through LDS.
-template <typename R, int TX, int TY, int ZC, int MODE, int NT, int WPE, bool HG>
-__global__ __attribute__((amdgpu_flat_work_group_size(1, NT), amdgpu_waves_per_eu(WPE)))
+// The workgroup's points are split over its threads anew for each stage, row
+// by row of the stage's own region, so that no wave works for the halo of
+// another stage: q over the plane with its 2-point halo (velocities,
+// physical trials), r over the centres with a 1-point halo, e over the edges
+// and faces.  What a stage takes from memory is loaded under the stage's own
+// split one step ahead, right after the previous step's values have been
+// used, into the same registers.
+template <typename R, int TX, int TY, int MODE, int NT, int WPE, bool HG, bool FRZ>
+__global__ __attribute__((amdgpu_flat_work_group_size(NT, NT), amdgpu_waves_per_eu(WPE)))
 void k_fused_3d(SweepArgs<R> a, TileSet ts)
 {
-    constexpr int W = TX + 4, H = TY + 4, N = W * H;
-    constexpr int NQ = (N + NT - 1) / NT;                  // plane positions per thread
-    constexpr int CW = TX + 2, CN = (TX + 2) * (TY + 2);   // centre region (1-cell halo)
-    constexpr int NR = (CN + NT - 1) / NT;
-    constexpr int NG = HG ? 2 : 1;
-    __shared__ R s_vx[2][N], s_vy[2][N], s_vz[2][N];
-    __shared__ R s_Sxy[N], s_Sxz[2][N], s_Syz[2][N];
-    __shared__ R s_lam[2][N], s_p[2][N], s_sxx[2][N], s_syy[2][N];
-    __shared__ R s_nxy[2][N], s_nxz[2][N], s_nyz[2][N];
-    __shared__ R s_ig[NG][HG ? N : 1];                    // per-cell 1/(G dt), two planes
-    __shared__ double s_red[NT / 64 > 0 ? NT / 64 : 1];
+    constexpr int W = TX + 4, H = TY + 4, N = W * H;       // plane with its halo
+    constexpr int CW = TX + 2, CN = CW * (TY + 2);         // centres
+    constexpr int EW = TX + 1, EN = EW * (TY + 1);         // edges, faces
+    constexpr int NP = N + 2;                              // + a place for the threads beyond the plane
+    constexpr int PAD = W + 2;                             // the halo's outermost points read neighbours before it
+    constexpr int NPAIR = L_PAIRS + (HG ? 1 : 0), SL = NPAIR * NP;
+    constexpr int RW = (CN + 63) / 64, QW = (EN + 63) / 64;   // waves with centres, with edges
+    static_assert(N <= NT, "one point per thread");
+    __shared__ R sm[PAD + 2 * SL + L_SINGLE * NP + PAD];
+    __shared__ double s_red[NT / 64];
 
     const int lb = xcd_remap(blockIdx.x, ts.nbx * ts.nby * ts.nbz);
     const int bx = lb % ts.nbx, by = (lb / ts.nbx) % ts.nby, bz = lb / (ts.nbx * ts.nby);
@@ -74,404 +120,337 @@ void k_fused_3d(SweepArgs<R> a, TileSet ts)
     constexpr bool INT = decltype(interior)::value;
     const int i0 = bx * TX, j0 = by * TY;
     const int nx = a.nx, ny = a.ny, nz = a.nz;
-    const int k0 = bz * ZC, k1 = min(k0 + ZC, nz);
-    const long sz = a.sz;
+    const int k0 = bz * ts.zc, k1 = min(k0 + ts.zc, nz);
     const int tid = threadIdx.x;
-    const int hx = (i0 + TX == nx) ? 1 : 0;     // owns the x = nx row when nx % TX == 0
-    const int hy = (j0 + TY == ny) ? 1 : 0;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int hx = (!INT && i0 + TX == nx) ? 1 : 0;     // owns the x = nx row when nx % TX == 0
+    const int hy = (!INT && j0 + TY == ny) ? 1 : 0;
     const bool last_z = (k1 == nz);
 
-    // Fields are addressed from the first field of their group (iteration
-    // k, k+1, increment start) and the uniform field stride fs, and points
-    // as a uniform plane address plus a 32-bit in-plane byte offset: the
-    // loads and stores take a scalar base and one vector offset, and the 26
-    // field pointers need not stay in scalar registers.  fs is made opaque
-    // to the compiler once per march step so that the field addresses are
-    // formed where they are used rather than hoisted out of the loop and
-    // kept live (spilled) over it.
-    const R* const itb = a.it[0];
-    R* const nxb = a.nx_[0];
-    const R* const olb = a.old[0];
-    long fs = a.fs;
-    auto ld = [](const R* pl, unsigned o) -> R { return *(const R*)((const char*)pl + o); };
-    auto st = [](R* pl, unsigned o, R v) { *(R*)((char*)pl + o) = v; };
-    auto off = [&](int i, int j) -> unsigned { return (unsigned)(i + a.sy * j) * (unsigned)sizeof(R); };
+    // fields: first plane of the chunk of the first field of a group, and the
+    // uniform field stride in bytes
+    const int kb = max(k0 - 2, 0), plane_bytes = (int)(a.sz * (long)sizeof(R));
+    const long first = (long)kb * a.sz;
+    const char* const itb = (const char*)(a.it[0] + first);
+    char* const nxb = (char*)(a.nx_[0] + first);
+    const char* const olb = (const char*)(a.old[0] + first);
+    const char* const cob = (const char*)((FRZ ? a.lam : a.coh) + first);
+    const char* const igb = HG ? (const char*)(a.igdc + first) : nullptr;
+    char* const lmb = (char*)(a.lam + first);
+    const bool keep_lam = !FRZ && a.lam_mode == LAM_STORE;
+    long fs = a.fs * (long)sizeof(R);
+    // byte offset of plane g in the chunk (planes outside the domain: the
+    // nearest; what is read there is not used)
+    auto plane = [&](int g) -> int { return (min(max(g, kb), nz) - kb) * plane_bytes; };
+    auto off = [&](bool ok, int i, int j) -> unsigned {
+        return ok && i >= 0 && i <= nx && j >= 0 && j <= ny ? (unsigned)(i + a.sy * j) * (unsigned)sizeof(R) : NOWHERE;
+    };
     const R idx = a.idx, idy = a.idy, idz = a.idz, igt = a.igt, igd = a.igd, ikt = a.ikt, ikd = a.ikd;
     const R D = a.D;
 
-    // per-thread positions: plane points q (S1, S2, S4, S5) and centre points r (S3)
-    int qi[NQ], qj[NQ];
-    unsigned qo[NQ];
-    bool qok[NQ];
-    for (int u = 0; u < NQ; ++u) {
-        const int q = tid + NT * u;
-        qok[u] = q < N;
-        qi[u] = i0 - 2 + q % W;
-        qj[u] = j0 - 2 + q / W;
-        qo[u] = off(qi[u], qj[u]);
-    }
-    int ri[NR], rj[NR];
-    unsigned ro[NR];
-    bool rok[NR];
-    for (int u = 0; u < NR; ++u) {
-        const int r = tid + NT * u;
-        rok[u] = r < CN;
-        ri[u] = i0 - 1 + r % CW;
-        rj[u] = j0 - 1 + r / CW;
-        ro[u] = off(ri[u], rj[u]);
-    }
+    // q: this thread's plane point
+    const int q = min(tid, N), qi = i0 - 2 + q % W, qj = j0 - 2 + q / W;
+    const unsigned qo = off(tid < N, qi, qj);
+    const bool q_xz = INT || (qi >= 1 && qi <= nx - 1 && qj >= 0 && qj < ny);
+    const bool q_yz = INT || (qj >= 1 && qj <= ny - 1 && qi >= 0 && qi < nx);
+    const bool q_xy = INT || (qi >= 1 && qi <= nx - 1 && qj >= 1 && qj <= ny - 1);
+    // r: this thread's centre
+    const int rr = min(tid, CN - 1), rla = 1 + rr % CW, rlb = 1 + rr / CW, rq = tid < CN ? rla + W * rlb : N;
+    const int ri = i0 - 2 + rla, rj = j0 - 2 + rlb;
+    const unsigned ro = off(tid < CN, ri, rj);
+    const bool r_in = INT || (ri >= 0 && ri < nx && rj >= 0 && rj < ny);
+    const bool r_own = tid < CN && r_in && rla >= 2 && rla < TX + 2 && rlb >= 2 && rlb < TY + 2;
+    const unsigned ros = r_own ? ro : NOWHERE;
+    // e: this thread's edge and face point
+    const int ee = min(tid, EN - 1), ela = 2 + ee % EW, elb = 2 + ee / EW, eq = tid < EN ? ela + W * elb : N;
+    const int ei = i0 - 2 + ela, ej = j0 - 2 + elb;
+    const unsigned eo = off(tid < EN, ei, ej);
+    const bool e_x = tid < EN && ela < TX + 2 + hx && (INT || ei <= nx), e_y = tid < EN && elb < TY + 2 + hy && (INT || ej <= ny);
+    const bool e_xc = tid < EN && ela < TX + 2 && (INT || ei < nx), e_yc = tid < EN && elb < TY + 2 && (INT || ej < ny);
+    const bool own_xy = e_x && e_y, own_xz = e_x && e_yc, own_yz = e_xc && e_y, own_c = e_xc && e_yc;
+    const bool in_x = INT || (ei >= 1 && ei <= nx - 1), in_y = INT || (ej >= 1 && ej <= ny - 1);
 
-    // prefetch registers (step g)
-    R fvx[NQ], fvy[NQ], fvz[NQ], fxz[NQ], fxzo[NQ], fyz[NQ], fyzo[NQ], fxy[NQ], fxyo[NQ], fig[NQ];
-    R fp[NR], fpo[NR], fsx[NR], fsxo[NR], fsy[NR], fsyo[NR], fc[NR];
-    auto prefetch = [&](int g) {
-        const bool pl = g >= 0 && g < nz, lv = g >= 0 && g <= nz, inner = g >= 1 && g <= nz - 1;
-        const bool pm = g - 1 >= 0 && g - 1 < nz;
-        const long pg = sz * g, pg1 = pg - sz;
-#pragma unroll
-        for (int u = 0; u < NQ; ++u) {
-            const int i = qi[u], j = qj[u];
-            const unsigned o = qo[u];
-            const bool ok = qok[u];
-            fvx[u] = (ok && pl && (INT || (i >= 0 && i <= nx && j >= 0 && j < ny))) ? ld(itb + F_VX * fs + pg, o) : R(0);
-            fvy[u] = (ok && pl && (INT || (i >= 0 && i < nx && j >= 0 && j <= ny))) ? ld(itb + F_VY * fs + pg, o) : R(0);
-            fvz[u] = (ok && lv && (INT || (i >= 0 && i < nx && j >= 0 && j < ny))) ? ld(itb + F_VZ * fs + pg, o) : R(0);
-            // edge stresses of iteration k wherever the edge exists (wall
-            // values enter the residual), increment-start values inside
-            const bool xz_in = INT || (i >= 0 && i <= nx && j >= 0 && j < ny);
-            const bool yz_in = INT || (i >= 0 && i < nx && j >= 0 && j <= ny);
-            const bool xy_in = INT || (i >= 0 && i <= nx && j >= 0 && j <= ny);
-            fxz[u] = (ok && lv && xz_in) ? ld(itb + F_TXZ * fs + pg, o) : R(0);
-            fyz[u] = (ok && lv && yz_in) ? ld(itb + F_TYZ * fs + pg, o) : R(0);
-            fxy[u] = (ok && pm && xy_in) ? ld(itb + F_TXY * fs + pg1, o) : R(0);
-            const bool exz = ok && inner && (INT || (i >= 1 && i <= nx - 1 && j >= 0 && j < ny));
-            const bool eyz = ok && inner && (INT || (j >= 1 && j <= ny - 1 && i >= 0 && i < nx));
-            fxzo[u] = exz ? ld(olb + O_TXZ * fs + pg, o) : R(0);
-            fyzo[u] = eyz ? ld(olb + O_TYZ * fs + pg, o) : R(0);
-            const bool exy = ok && pm && (INT || (i >= 1 && i <= nx - 1 && j >= 1 && j <= ny - 1));
-            fxyo[u] = exy ? ld(olb + O_TXY * fs + pg1, o) : R(0);
-            if (HG)
-                fig[u] = (ok && pl && (INT || (i >= 0 && i < nx && j >= 0 && j < ny))) ? ld(a.igdc + pg, o) : R(0);
-        }
-#pragma unroll
-        for (int u = 0; u < NR; ++u) {
-            const int i = ri[u], j = rj[u];
-            const unsigned o = ro[u];
-            const bool ok = rok[u] && pm && (INT || (i >= 0 && i < nx && j >= 0 && j < ny));
-            fp[u] = ok ? ld(itb + F_P * fs + pg1, o) : R(0);
-            fpo[u] = ok ? ld(olb + O_P * fs + pg1, o) : R(0);
-            fsx[u] = ok ? ld(itb + F_TXX * fs + pg1, o) : R(0);
-            fsxo[u] = ok ? ld(olb + O_TXX * fs + pg1, o) : R(0);
-            fsy[u] = ok ? ld(itb + F_TYY * fs + pg1, o) : R(0);
-            fsyo[u] = ok ? ld(olb + O_TYY * fs + pg1, o) : R(0);
-            fc[u] = ok ? ld(a.coh + pg1, o) : R(0);
-        }
+    R* const s0 = sm + PAD;
+    R* const s1 = s0 + 2 * SL;
+
+    // velocities of plane (vx, vy) and level (vz) g, and the compliances
+    R fvx, fvy, fvz, fig = R(0);
+    auto load_v = [&](int g) {
+        const int p = plane(g);
+        const bool go = g <= k1 + 1;
+        fvx = buf_load<R>(itb, go, qo, p);
+        fvy = buf_load<R>(itb + fs, go, qo, p);
+        fvz = buf_load<R>(itb + fs + fs, go, qo, p);
+        if (HG) fig = buf_load<R>(igb, go, qo, p);
+    };
+    auto stage_v = [&](int slot) {
+        R* const s = s0 + slot * SL + q;
+        s[L_VX * NP] = fvx;
+        s[L_VY * NP] = fvy;
+        s[L_VZ * NP] = fvz;
+        if (HG) s[L_IG * NP] = fig;
+    };
+    // increment-start edge stresses: xz, yz at level f, xy at plane f - 1
+    R oxz, oyz, oxy;
+    auto load_old = [&](int f) {
+        const char* b = olb + 3 * fs;
+        const bool go = f <= k1 + 1;
+        oxy = buf_load<R>(b, go, qo, plane(f - 1));
+        b += fs;
+        oxz = buf_load<R>(b, go, qo, plane(f));
+        b += fs;
+        oyz = buf_load<R>(b, go, qo, plane(f));
+    };
+    // centre data of plane c
+    R cp, cpo, csx, csxo, csy, csyo, cc;
+    auto load_c = [&](int c) {
+        const int p = plane(c);
+        const bool go = c >= k0 - 1 && c <= k1;
+        const char *b = itb + 3 * fs, *o = olb;
+        cp = buf_load<R>(b, go, ro, p);
+        cpo = buf_load<R>(o, go, ro, p);
+        b += fs;
+        o += fs;
+        csx = buf_load<R>(b, go, ro, p);
+        csxo = buf_load<R>(o, go, ro, p);
+        b += fs;
+        o += fs;
+        csy = buf_load<R>(b, go, ro, p);
+        csyo = buf_load<R>(o, go, ro, p);
+        cc = buf_load<R>(cob, go, ro, p);
+    };
+    // edge stresses of iteration k of plane and level l
+    R kxy, kxz, kyz;
+    auto load_k = [&](int l) {
+        const int p = plane(l);
+        const bool go = l >= k0 && l <= k1;
+        const char* b = itb + 6 * fs;
+        kxy = buf_load<R>(b, go, eo, p);
+        b += fs;
+        kxz = buf_load<R>(b, go, eo, p);
+        b += fs;
+        kyz = buf_load<R>(b, go, eo, p);
+    };
+    // velocities of iteration k at the faces: vx, vy of plane p, vz of level p + 1
+    R wvx, wvy, wvz;
+    auto load_w = [&](int p) {
+        const bool go = p >= k0 - 1 && p <= k1;
+        wvx = buf_load<R>(itb, go, eo, plane(p));
+        wvy = buf_load<R>(itb + fs, go, eo, plane(p));
+        wvz = buf_load<R>(itb + fs + fs, go, eo, plane(p + 1));
     };
 
     // combined, momentum-only, |v|, |stress| maxima, kept in the field type
     // (maxima are exact) and widened for the block reduction
     R rmax = R(0), mmax = R(0), vmax = R(0), smax = R(0);
+    // compliances of the xz, yz edges of the level of the next step
+    R pgxz = igd, pgyz = igd;
+    // of the previous step: sums of the Lambda of the plane's two centres at
+    // the xz and yz edges, new xz and yz stresses, -sigma_zz, and the parts of
+    // the x and y momentum residuals within the plane
+    R mxz = R(0), myz = R(0), uxz = R(0), uyz = R(0), uzz = R(0), ux = R(0), uy = R(0);
+    R txy = R(0), txz = R(0), tyz = R(0);      // new edge stresses of this step
 
-    // S1 of step g: the prefetched velocities of plane g (vx, vy) and level
-    // g (vz), and the compliances of plane g, go to LDS and the velocities
-    // into this thread's register history, from which S5 takes the old
-    // velocities of its own points (vx, vy of plane g-2, vz of level g-1 at
-    // step g)
-    R hvx1[NQ], hvx2[NQ], hvx3[NQ], hvy1[NQ], hvy2[NQ], hvy3[NQ], hvz1[NQ], hvz2[NQ];
-    auto stage_velocities = [&](int g) {
-        const bool ld_xy = g >= 0 && g < nz;
-        const bool ld_z = g >= 0 && g <= nz;
-        const int s2 = mod2(g);
-#pragma unroll
-        for (int u = 0; u < NQ; ++u) {
-            hvx3[u] = hvx2[u]; hvx2[u] = hvx1[u]; hvx1[u] = fvx[u];
-            hvy3[u] = hvy2[u]; hvy2[u] = hvy1[u]; hvy1[u] = fvy[u];
-            hvz2[u] = hvz1[u]; hvz1[u] = fvz[u];
-            if (!qok[u]) continue;
-            const int q = tid + NT * u;
-            if (ld_xy) {
-                s_vx[s2][q] = fvx[u];
-                s_vy[s2][q] = fvy[u];
-                if (HG) s_ig[s2 & (NG - 1)][q] = fig[u];
-            }
-            if (ld_z) s_vz[s2][q] = fvz[u];
-        }
-    };
-#pragma unroll
-    for (int u = 0; u < NQ; ++u) {
-        hvx1[u] = hvx2[u] = hvx3[u] = R(0);
-        hvy1[u] = hvy2[u] = hvy3[u] = R(0);
-        hvz1[u] = hvz2[u] = R(0);
-    }
-    // edge stresses of iteration k at the level of the previous step (xz,
-    // yz), and with a per-cell G the edge compliances of this step (xy at
-    // plane f-1; xz, yz at level f) and of the previous step (xz, yz)
-    R pcxz[NQ], pcyz[NQ], gxy[NQ], gxz[NQ], gyz[NQ], pgxz[NQ], pgyz[NQ];
-#pragma unroll
-    for (int u = 0; u < NQ; ++u) {
-        pcxz[u] = pcyz[u] = R(0);
-        gxy[u] = gxz[u] = gyz[u] = pgxz[u] = pgyz[u] = igd;
-    }
-    prefetch(k0 - 2);
-    stage_velocities(k0 - 2);
+    load_v(k0 - 2);
+    stage_v(k0 & 1);
+    load_v(k0 - 1);
+    stage_v((k0 & 1) ^ 1);
+    load_old(k0 - 1);
+    load_c(k0 - 2);
+    load_k(k0 - 2);
+    load_w(k0 - 3);
+    load_v(k0);
     __syncthreads();
-    for (int f = k0 - 2; f <= k1 + 1; ++f) {
+    // f - 1 is the plane of the centres, f - 2 that of the vx and vy updates
+    for (int f = k0 - 1; f <= k1 + 1; ++f) {
         asm volatile("" : "+s"(fs));
-        // take over the data of step f, start loading step f+1
-        R cxz[NQ], cxzo[NQ], cyz[NQ], cyzo[NQ], cxy[NQ], cxyo[NQ];
-        R cp[NR], cpo[NR], csx[NR], csxo[NR], csy[NR], csyo[NR], cc[NR];
-#pragma unroll
-        for (int u = 0; u < NQ; ++u) {
-            cxz[u] = fxz[u]; cxzo[u] = fxzo[u]; cyz[u] = fyz[u]; cyzo[u] = fyzo[u];
-            cxy[u] = fxy[u]; cxyo[u] = fxyo[u];
-            if (HG) { pgxz[u] = gxz[u]; pgyz[u] = gyz[u]; }
-        }
-#pragma unroll
-        for (int u = 0; u < NR; ++u) {
-            cp[u] = fp[u]; cpo[u] = fpo[u]; csx[u] = fsx[u]; csxo[u] = fsxo[u];
-            csy[u] = fsy[u]; csyo[u] = fsyo[u]; cc[u] = fc[u];
-        }
-        if (f + 1 <= k1 + 1) prefetch(f + 1);
+        const int sc = f & 1;                 // slot of plane f; plane f - 1 has the other one
+        R* const sf = s0 + sc * SL;
+        R* const sg = s0 + (sc ^ 1) * SL;
 
         // ---- S2: physical shear trials: xz, yz at level f; xy at plane f-1 --
         {
-            const bool do_l = f >= k0 - 1 && f >= 0 && f <= nz;
-            const bool do_p = f - 1 >= k0 - 1 && f - 1 >= 0 && f - 1 < nz;
-            const int l = f, sl = mod2(l), cm = mod2(l), cp3 = mod2(l - 1), pm = mod2(f - 1);
-            const bool inner_l = l >= 1 && l <= nz - 1;
-#pragma unroll
-            for (int u = 0; u < NQ; ++u) {
-                const int q = tid + NT * u;
-                if (!qok[u] || q % W < 1 || q / W < 1) continue;
-                const int i = qi[u], j = qj[u];
-                if (do_l) {
-                    R sxz = R(0), syz = R(0);
-                    if (HG) {       // compliance of an edge: mean of its four cells
-                        const int a0 = sl & (NG - 1), a1 = cp3 & (NG - 1);
-                        gxz[u] = inner_l ? R(0.25) * (s_ig[a1][q - 1] + s_ig[a1][q] + s_ig[a0][q - 1] + s_ig[a0][q]) : igd;
-                        gyz[u] = inner_l ? R(0.25) * (s_ig[a1][q - W] + s_ig[a1][q] + s_ig[a0][q - W] + s_ig[a0][q]) : igd;
-                    }
-                    if (inner_l && (INT || (i >= 1 && i <= nx - 1 && j >= 0 && j < ny))) {
-                        R e2 = (s_vx[cm][q] - s_vx[cp3][q]) * idz + (s_vz[sl][q] - s_vz[sl][q - 1]) * idx;
-                        sxz = cxzo[u] * (HG ? gxz[u] : igd) + e2;
-                    }
-                    if (inner_l && (INT || (j >= 1 && j <= ny - 1 && i >= 0 && i < nx))) {
-                        R e2 = (s_vy[cm][q] - s_vy[cp3][q]) * idz + (s_vz[sl][q] - s_vz[sl][q - W]) * idy;
-                        syz = cyzo[u] * (HG ? gyz[u] : igd) + e2;
-                    }
-                    s_Sxz[sl][q] = sxz;
-                    s_Syz[sl][q] = syz;
-                }
-                if (do_p) {
-                    R t = R(0);
-                    if (HG) {
-                        const int a0 = pm & (NG - 1);
-                        gxy[u] = R(0.25) * (s_ig[a0][q - W - 1] + s_ig[a0][q - W] + s_ig[a0][q - 1] + s_ig[a0][q]);
-                    }
-                    if (INT || (i >= 1 && i <= nx - 1 && j >= 1 && j <= ny - 1)) {
-                        R e2 = (s_vx[pm][q] - s_vx[pm][q - W]) * idy + (s_vy[pm][q] - s_vy[pm][q - 1]) * idx;
-                        t = cxyo[u] * (HG ? gxy[u] : igd) + e2;
-                    }
-                    s_Sxy[q] = t;
-                }
+            R* const cu = sf + q;             // plane / level f
+            R* const pr = sg + q;             // plane f - 1
+            const bool inner = f >= 1 && f <= nz - 1;
+            R gxy = igd, gxz = igd, gyz = igd;
+            if (HG) {                         // compliance of an edge: mean of its four cells
+                const R *c0 = cu + L_IG * NP, *c1 = pr + L_IG * NP;
+                gxz = R(0.25) * (c1[-1] + c1[0] + c0[-1] + c0[0]);
+                gyz = R(0.25) * (c1[-W] + c1[0] + c0[-W] + c0[0]);
+                gxy = R(0.25) * (c1[-W - 1] + c1[-W] + c1[-1] + c1[0]);
             }
+            const R vz0 = cu[L_VZ * NP], vx0 = cu[L_VX * NP], vy0 = cu[L_VY * NP];
+            const R vx1 = pr[L_VX * NP], vy1 = pr[L_VY * NP];
+            const R exz = (vx0 - vx1) * idz + (vz0 - cu[L_VZ * NP - 1]) * idx;
+            const R eyz = (vy0 - vy1) * idz + (vz0 - cu[L_VZ * NP - W]) * idy;
+            const R exy = (vx1 - pr[L_VX * NP - W]) * idy + (vy1 - pr[L_VY * NP - 1]) * idx;
+            const R sxz = oxz * gxz + exz, syz = oyz * gyz + eyz, sxy = oxy * gxy + exy;
+            cu[L_SXZ * NP] = inner && q_xz ? sxz : R(0);
+            cu[L_SYZ * NP] = inner && q_yz ? syz : R(0);
+            s1[L_SXY * NP + q] = q_xy ? sxy : R(0);
         }
+        load_old(f + 1);
         __syncthreads();
         // ---- S3: centres of plane c = f-1 -----------------------------------
-        const int c = f - 1;
-        if (c >= k0 - 1 && c >= 0 && c < nz && c <= k1) {
-            const int cm = mod2(c), sc = mod2(c), sc1 = mod2(c + 1);
-#pragma unroll
-            for (int u = 0; u < NR; ++u) {
-                if (!rok[u]) continue;
-                const int r = tid + NT * u;
-                const int la = 1 + r % CW, lbb = 1 + r / CW;
-                const int q = la + W * lbb;
-                const int i = ri[u], j = rj[u];
-                if (!INT && !(i >= 0 && i < nx && j >= 0 && j < ny)) {
-                    s_lam[sc][q] = R(0);
-                    s_p[sc][q] = R(0);
-                    s_sxx[sc][q] = R(0);
-                    s_syy[sc][q] = R(0);
-                    continue;
-                }
-                R dvx = (s_vx[cm][q + 1] - s_vx[cm][q]) * idx + a.ebx;
-                R dvy = (s_vy[cm][q + W] - s_vy[cm][q]) * idy + a.eby;
-                R dvz = (s_vz[sc1][q] - s_vz[sc][q]) * idz + a.ebz;
+        {
+            const int c = f - 1;
+            R pn = R(0), txx = R(0), tyy = R(0), lam = R(0);
+            if (wave < RW) {
+                const R* const up = sf + rq;  // level c + 1
+                const R* const at = sg + rq;  // plane, level c
+                const R vz0 = at[L_VZ * NP];
+                R dvx = (at[L_VX * NP + 1] - at[L_VX * NP]) * idx + a.ebx;
+                R dvy = (at[L_VY * NP + W] - at[L_VY * NP]) * idy + a.eby;
+                R dvz = (up[L_VZ * NP] - vz0) * idz + a.ebz;
                 R div = dvx + dvy + dvz;
-                const R pk = cp[u], txk = csx[u], tyk = csy[u];
-                R pn = (pk * ikt + cpo[u] * ikd - div) * a.ikk;
+                const R pk = cp, txk = csx, tyk = csy;
+                pn = (pk * ikt + cpo * ikd - div) * a.ikk;
                 // per-cell G: the cell's compliance, its physical Dp and its D
-                const R igc = HG ? s_ig[cm & (NG - 1)][q] : igd;
+                const R igc = HG ? at[L_IG * NP] : igd;
                 const R Dp = HG ? igc + a.imus : a.Dp;
                 const R invDp = HG ? fast_rcp(Dp) : a.invDp;
                 const R Dc = HG ? igt + Dp : D;
                 const R invDc = HG ? fast_rcp(Dc) : a.invD;
-                const R Sxx = csxo[u] * igc + R(2) * (dvx - div * R(1.0 / 3.0));
-                const R Syy = csyo[u] * igc + R(2) * (dvy - div * R(1.0 / 3.0));
+                const R Sxx = csxo * igc + R(2) * (dvx - div * R(1.0 / 3.0));
+                const R Syy = csyo * igc + R(2) * (dvy - div * R(1.0 / 3.0));
                 const R Szz = -(Sxx + Syy);
                 const R Txx = txk * igt + Sxx, Tyy = tyk * igt + Syy, Tzz = -(Txx + Tyy);
-                const R Sxyb = R(0.25) * (s_Sxy[q] + s_Sxy[q + 1] + s_Sxy[q + W] + s_Sxy[q + W + 1]);
-                const R Sxzb = R(0.25) * (s_Sxz[sc][q] + s_Sxz[sc][q + 1] + s_Sxz[sc1][q] + s_Sxz[sc1][q + 1]);
-                const R Syzb = R(0.25) * (s_Syz[sc][q] + s_Syz[sc][q + W] + s_Syz[sc1][q] + s_Syz[sc1][q + W]);
+                R* const one = s1 + rq;
+                const R* const xy = one + L_SXY * NP;
+                const R Sxyb = R(0.25) * (xy[0] + xy[1] + xy[W] + xy[W + 1]);
+                const R Sxzb = R(0.25) * (at[L_SXZ * NP] + at[L_SXZ * NP + 1] + up[L_SXZ * NP] + up[L_SXZ * NP + 1]);
+                const R Syzb = R(0.25) * (at[L_SYZ * NP] + at[L_SYZ * NP + W] + up[L_SYZ * NP] + up[L_SYZ * NP + W]);
                 const R nS2 = R(0.5) * (Sxx * Sxx + Syy * Syy + Szz * Szz);
                 const R sh2 = Sxyb * Sxyb + Sxzb * Sxzb + Syzb * Syzb;
                 const R ptr = pn;
-                const bool own = la >= 2 && la < TX + 2 && lbb >= 2 && lbb < TY + 2 && c >= k0 && c < k1;
-                R lam;
-                if (a.lam_mode == LAM_FROZEN) {                  // frozen plasticity: the held Lambda
-                    lam = ld(a.lam + sz * c, ro[u]);
+                if (FRZ) {                                       // frozen plasticity: the held Lambda
+                    lam = cc;
                     // dilatancy of the held Lambda: lamdot = Lambda sqrt(J2(S)) / (Dp + Lambda)
                     if (a.Cik != R(0)) pn = ptr + lam * fast_sqrt(nS2 + sh2) * fast_rcp(Dp + lam) * a.Cik;
                 } else {
                     lam = centre_return(R(0.5) * (Txx * Txx + Tyy * Tyy + Tzz * Tzz), nS2, sh2, Dp, invDp, Dc, invDc,
-                                        pn, cc[u], a.A, a.B, a.Cik, a.vp, a.blend);
-                    if (a.lam_mode != LAM_COMPUTE && own) st(a.lam + sz * c, ro[u], lam);     // stored for freezing
+                                        pn, cc, a.A, a.B, a.Cik, a.vp, a.blend);
                 }
                 const R sc_ = fast_rcp(Dc + lam);
-                R txx = Txx * sc_, tyy = Tyy * sc_;
-                s_lam[sc][q] = lam;
-                s_p[sc][q] = pn;
-                s_sxx[sc][q] = txx;
-                s_syy[sc][q] = tyy;
-                if (own) {
-                    const long pc = sz * c;
-                    st(nxb + F_P * fs + pc, ro[u], pn);
-                    st(nxb + F_TXX * fs + pc, ro[u], txx);
-                    st(nxb + F_TYY * fs + pc, ro[u], tyy);
-                    if (MODE == MODE_CHECK) {
-                        R dp = fabs(pn - pk) * a.rK;
-                        R dtx = fabs(txx - txk), dty = fabs(tyy - tyk), dtz = fabs((txx + tyy) - (txk + tyk));
-                        rmax = nmax(rmax, nmax(dp, nmax(nmax(dtx, dty), dtz) * a.rG));
-                        smax = nmax(smax, nmax(nmax(fabs(pn), fabs(txx)), nmax(fabs(tyy), fabs(txx + tyy))));
-                    }
+                txx = opaque(Txx * sc_);
+                tyy = opaque(Tyy * sc_);
+                pn = opaque(pn);
+                if (!INT && !r_in) lam = pn = txx = tyy = R(0);
+                one[L_LAM * NP] = lam;
+                one[L_XX * NP] = txx - pn;
+                one[L_YY * NP] = tyy - pn;
+                one[L_ZZ * NP] = -(txx + tyy) - pn;
+                if (MODE == MODE_CHECK && r_own && c >= k0 && c < k1) {
+                    R dp = fabs(pn - pk) * a.rK;
+                    R dtx = fabs(txx - txk), dty = fabs(tyy - tyk), dtz = fabs((txx + tyy) - (txk + tyk));
+                    rmax = nmax(rmax, nmax(dp, nmax(nmax(dtx, dty), dtz) * a.rG));
+                    smax = nmax(smax, nmax(nmax(fabs(pn), fabs(txx)), nmax(fabs(tyy), fabs(txx + tyy))));
                 }
             }
+            const bool go = c >= k0 && c < k1;
+            const int p = plane(c);
+            char* b = nxb + 3 * fs;
+            buf_store(b, go, ros, p, pn);
+            b += fs;
+            buf_store(b, go, ros, p, txx);
+            b += fs;
+            buf_store(b, go, ros, p, tyy);
+            if (keep_lam) buf_store(lmb, go, ros, p, lam);       // stored for freezing
         }
+        load_c(f);
         __syncthreads();
-        // ---- S4: new edge stresses: xy at plane f-1, xz / yz at level f-1,
-        //      at this thread's own edge points: T = tau_k/(G~ dtau) + S ------
+        // ---- S4: new edge stresses: xy at plane f-1, xz / yz at level f-1:
+        //      T = tau_k/(G~ dtau) + S ------------------------------------------
         {
-            const int p = f - 1, l = f - 1;
-            const bool do_p = p >= k0 && p < k1;
-            const bool do_l = l >= k0 && l <= k1 && l >= 0 && l <= nz;
-            const int sp = mod2(p), sl = mod2(l), sm = mod2(l - 1);
-            const bool inner_l = l >= 1 && l <= nz - 1;
-            const bool own_l = l < k1 || (l == nz && last_z);
-#pragma unroll
-            for (int u = 0; u < NQ; ++u) {
-                const int q = tid + NT * u;
-                const int la = q % W, lbb = q / W;
-                if (!qok[u] || la < 2 || la > TX + 2 || lbb < 2 || lbb > TY + 2) continue;
-                const int i = qi[u], j = qj[u];
-                const unsigned o = qo[u];
-                if (do_p) {
-                    R t = R(0);
-                    if (INT || (i >= 1 && i <= nx - 1 && j >= 1 && j <= ny - 1)) {
-                        R lv = R(0.25) * (s_lam[sp][q - W - 1] + s_lam[sp][q - W] + s_lam[sp][q - 1] + s_lam[sp][q]);
-                        const R De = HG ? igt + gxy[u] + a.imus : D;
-                        t = (cxy[u] * igt + s_Sxy[q]) * fast_rcp(De + lv);
-                    }
-                    s_nxy[sp][q] = t;
-                    if (la < TX + 2 + hx && lbb < TY + 2 + hy && (INT || (i <= nx && j <= ny))) {
-                        st(nxb + F_TXY * fs + sz * p, o, t);
-                        if (MODE == MODE_CHECK) rmax = nmax(rmax, fabs(t - cxy[u]) * a.rG);
-                    }
+            const int l = f - 1;
+            const bool do_p = l >= k0 && l < k1, inner = l >= 1 && l <= nz - 1;
+            const bool do_l = do_p || (l == nz && last_z);
+            uxz = txz;
+            uyz = tyz;
+            if (wave < QW) {
+                const R* const at = sg + eq;                    // level l
+                R* const one = s1 + eq;
+                const R* const la = one + L_LAM * NP;
+                R gxy = igd, gxz = pgxz, gyz = pgyz;
+                if (HG) {
+                    const R *c0 = sf + L_IG * NP + eq, *c1 = sg + L_IG * NP + eq;
+                    gxy = R(0.25) * (c1[-W - 1] + c1[-W] + c1[-1] + c1[0]);
+                    pgxz = R(0.25) * (c1[-1] + c1[0] + c0[-1] + c0[0]);
+                    pgyz = R(0.25) * (c1[-W] + c1[0] + c0[-W] + c0[0]);
                 }
-                if (do_l) {
-                    const long pl = sz * l;
-                    // xz edge (i, j) at level l: x-extent nx+1, y-extent ny
-                    if (lbb < TY + 2) {
-                        R t = R(0);
-                        if (inner_l && (INT || (i >= 1 && i <= nx - 1 && j < ny))) {
-                            R lv = R(0.25) * (s_lam[sm][q - 1] + s_lam[sm][q] + s_lam[sl][q - 1] + s_lam[sl][q]);
-                            const R De = HG ? igt + pgxz[u] + a.imus : D;
-                            t = (pcxz[u] * igt + s_Sxz[sl][q]) * fast_rcp(De + lv);
-                        }
-                        s_nxz[sl][q] = t;
-                        if (own_l && la < TX + 2 + hx && (INT || (i <= nx && j < ny))) {
-                            st(nxb + F_TXZ * fs + pl, o, t);
-                            if (MODE == MODE_CHECK) rmax = nmax(rmax, fabs(t - pcxz[u]) * a.rG);
-                        }
-                    }
-                    // yz edge (i, j) at level l: x-extent nx, y-extent ny+1
-                    if (la < TX + 2) {
-                        R t = R(0);
-                        if (inner_l && (INT || (j >= 1 && j <= ny - 1 && i < nx))) {
-                            R lv = R(0.25) * (s_lam[sm][q - W] + s_lam[sm][q] + s_lam[sl][q - W] + s_lam[sl][q]);
-                            const R De = HG ? igt + pgyz[u] + a.imus : D;
-                            t = (pcyz[u] * igt + s_Syz[sl][q]) * fast_rcp(De + lv);
-                        }
-                        s_nyz[sl][q] = t;
-                        if (own_l && lbb < TY + 2 + hy && (INT || (i < nx && j <= ny))) {
-                            st(nxb + F_TYZ * fs + pl, o, t);
-                            if (MODE == MODE_CHECK) rmax = nmax(rmax, fabs(t - pcyz[u]) * a.rG);
-                        }
-                    }
+                const R l00 = la[0], l01 = la[-1], l10 = la[-W];
+                const R vxy = R(0.25) * (la[-W - 1] + l10 + l01 + l00);
+                const R vxz = R(0.25) * (mxz + l01 + l00);
+                const R vyz = R(0.25) * (myz + l10 + l00);
+                mxz = l01 + l00;
+                myz = l10 + l00;
+                txy = (kxy * igt + one[L_SXY * NP]) * fast_rcp((HG ? igt + gxy + a.imus : D) + vxy);
+                txz = (kxz * igt + at[L_SXZ * NP]) * fast_rcp((HG ? igt + gxz + a.imus : D) + vxz);
+                tyz = (kyz * igt + at[L_SYZ * NP]) * fast_rcp((HG ? igt + gyz + a.imus : D) + vyz);
+                if (!INT && !(in_x && in_y)) txy = R(0);
+                if (!inner || (!INT && !(in_x && e_yc))) txz = R(0);
+                if (!inner || (!INT && !(in_y && e_xc))) tyz = R(0);
+                one[L_NXY * NP] = txy;
+                one[L_NXZ * NP] = txz;
+                one[L_NYZ * NP] = tyz;
+                if (MODE == MODE_CHECK) {
+                    if (do_p && own_xy) rmax = nmax(rmax, fabs(txy - kxy) * a.rG);
+                    if (do_l && own_xz) rmax = nmax(rmax, fabs(txz - kxz) * a.rG);
+                    if (do_l && own_yz) rmax = nmax(rmax, fabs(tyz - kyz) * a.rG);
                 }
             }
+            const int p = plane(l);
+            char* b = nxb + 6 * fs;
+            buf_store(b, do_p, own_xy ? eo : NOWHERE, p, txy);
+            b += fs;
+            buf_store(b, do_l, own_xz ? eo : NOWHERE, p, txz);
+            b += fs;
+            buf_store(b, do_l, own_yz ? eo : NOWHERE, p, tyz);
         }
-#pragma unroll
-        for (int u = 0; u < NQ; ++u) {      // this step's level becomes the previous one
-            pcxz[u] = cxz[u];
-            pcyz[u] = cyz[u];
-        }
+        load_k(f);
         __syncthreads();
-        // ---- S5: velocities: vx, vy at plane f-2, vz at level f-1, at this
-        //      thread's own plane points; then S1 of step f+1 ----------------
+        // ---- S5: velocities: vx, vy at plane f-2, vz at level f-1 ------------
         {
             const int p = f - 2, l = f - 1;
             const bool do_xy = p >= k0 && p < k1;
-            const bool do_z = l >= 0 && ((l >= k0 && l < k1) || (l == nz && last_z));
-            const int sp = mod2(p), sp1 = mod2(p + 1), sl = mod2(l), sm = mod2(l - 1);
-            const bool inner_l = l >= 1 && l <= nz - 1;
-#pragma unroll
-            for (int u = 0; u < NQ; ++u) {
-                const int q = tid + NT * u;
-                const int la = q % W, lbb = q / W, i = qi[u], j = qj[u];
-                if (!qok[u] || la < 2 || lbb < 2) continue;
-                if (do_xy) {
-                    const long pp = sz * p;
-                    if (la < TX + 2 + hx && lbb < TY + 2 && (INT || (i <= nx && j < ny))) {      // x-face
-                        R v = hvx3[u];
-                        if (INT || (i >= 1 && i <= nx - 1)) {
-                            R Rx = ((s_sxx[sp][q] - s_p[sp][q]) - (s_sxx[sp][q - 1] - s_p[sp][q - 1])) * idx
-                                 + (s_nxy[sp][q + W] - s_nxy[sp][q]) * idy + (s_nxz[sp1][q] - s_nxz[sp][q]) * idz;
-                            v = v + a.dtrho * Rx;
-                            mmax = nmax(mmax, fabs(Rx));
-                        }
-                        if (MODE != MODE_PHYS) st(nxb + F_VX * fs + pp, qo[u], v);
-                        vmax = nmax(vmax, fabs(v));
-                    }
-                    if (la < TX + 2 && lbb < TY + 2 + hy && (INT || (i < nx && j <= ny))) {      // y-face
-                        R v = hvy3[u];
-                        if (INT || (j >= 1 && j <= ny - 1)) {
-                            R Ry = (s_nxy[sp][q + 1] - s_nxy[sp][q]) * idx
-                                 + ((s_syy[sp][q] - s_p[sp][q]) - (s_syy[sp][q - W] - s_p[sp][q - W])) * idy
-                                 + (s_nyz[sp1][q] - s_nyz[sp][q]) * idz;
-                            v = v + a.dtrho * Ry;
-                            mmax = nmax(mmax, fabs(Ry));
-                        }
-                        if (MODE != MODE_PHYS) st(nxb + F_VY * fs + pp, qo[u], v);
-                        vmax = nmax(vmax, fabs(v));
-                    }
-                }
-                if (do_z && la < TX + 2 && lbb < TY + 2 && (INT || (i < nx && j < ny))) {
-                    R v = hvz2[u];
-                    if (inner_l) {
-                        R szu = -(s_sxx[sl][q] + s_syy[sl][q]) - s_p[sl][q];
-                        R szd = -(s_sxx[sm][q] + s_syy[sm][q]) - s_p[sm][q];
-                        R Rz = (s_nxz[sl][q + 1] - s_nxz[sl][q]) * idx + (s_nyz[sl][q + W] - s_nyz[sl][q]) * idy
-                             + (szu - szd) * idz;
-                        v = v + a.dtrho * Rz;
-                        mmax = nmax(mmax, fabs(Rz));
-                    }
-                    if (MODE != MODE_PHYS) st(nxb + F_VZ * fs + sz * l, qo[u], v);
-                    vmax = nmax(vmax, fabs(v));
+            const bool do_z = (l >= k0 && l < k1) || (l == nz && last_z);
+            const bool inner = l >= 1 && l <= nz - 1;
+            R vx = wvx, vy = wvy, vz = wvz;
+            if (wave < QW) {
+                const R* const one = s1 + eq;                   // plane, level l = p + 1
+                R Rx = ux + (txz - uxz) * idz;
+                R Ry = uy + (tyz - uyz) * idz;
+                R Rz = (one[L_NXZ * NP + 1] - txz) * idx + (one[L_NYZ * NP + W] - tyz) * idy + (one[L_ZZ * NP] - uzz) * idz;
+                ux = (one[L_XX * NP] - one[L_XX * NP - 1]) * idx + (one[L_NXY * NP + W] - txy) * idy;
+                uy = (one[L_NXY * NP + 1] - txy) * idx + (one[L_YY * NP] - one[L_YY * NP - W]) * idy;
+                uzz = one[L_ZZ * NP];
+                if (!INT && !in_x) Rx = R(0);
+                if (!INT && !in_y) Ry = R(0);
+                if (!inner) Rz = R(0);
+                vx = vx + a.dtrho * Rx;
+                vy = vy + a.dtrho * Ry;
+                vz = vz + a.dtrho * Rz;
+                if (MODE != MODE_UPDATE) {
+                    const bool ox = do_xy && own_xz, oy = do_xy && own_yz, oz = do_z && own_c;
+                    if (ox) mmax = nmax(mmax, fabs(Rx));
+                    if (oy) mmax = nmax(mmax, fabs(Ry));
+                    if (oz) mmax = nmax(mmax, fabs(Rz));
+                    if (ox) vmax = nmax(vmax, fabs(vx));
+                    if (oy) vmax = nmax(vmax, fabs(vy));
+                    if (oz) vmax = nmax(vmax, fabs(vz));
                 }
             }
+            if (MODE != MODE_PHYS) {
+                buf_store(nxb, do_xy, own_xz ? eo : NOWHERE, plane(p), vx);
+                buf_store(nxb + fs, do_xy, own_yz ? eo : NOWHERE, plane(p), vy);
+                buf_store(nxb + fs + fs, do_z, own_c ? eo : NOWHERE, plane(l), vz);
+            }
         }
-        if (f + 1 <= k1 + 1) stage_velocities(f + 1);
+        load_w(f - 1);
+        // ---- S1 of step f + 1 -------------------------------------------------
+        stage_v(sc ^ 1);
+        load_v(f + 2);
         __syncthreads();
     }
     if (MODE != MODE_UPDATE) {
@@ -487,29 +466,32 @@ void k_fused_3d(SweepArgs<R> a, TileSet ts)
     else body(std::false_type{});
 }
 
-// Tile shapes and workgroup sizes (X, Y: column; Z: planes per chunk; T:
-// threads; E: waves per SIMD to fit in registers, two FP32 workgroups per
-// CU).  FP32 has two shapes, both with 768 threads covering the halo plane
-// and every later stage in a single pass (no wave does a second round while
-// the others wait at a stage barrier), 72-73 KB of LDS:
-//  - 48 x 10 (52 x 14 = 728 plane points): rows of 52 values touch fewer
-//    partly used 128-byte lines per value than the 36 of a 32-wide tile
-//    (measured at 511^3: 2.14x against 2.35x the algorithmic reads, 4.10
-//    against 4.30 ms per sweep; 64 x 7, 56 x 8, 40 x 13 and 48 x 9 slower);
-//  - 32 x 16 (36 x 20 = 720 points), which fits grids of 32-cell multiples
-//    with fewer workgroups (255^3: 1024 workgroups, two full rounds of 512,
-//    0.585 ms, against 1248 and 0.618 ms for 48 x 10).
-// FP64: 32 x 16 tiles with 768 threads as well (144-154 KB of LDS, one
-// workgroup and three waves per SIMD per CU, the occupancy three 256-thread
-// 16 x 8 workgroups had): the wider halo plane cuts the re-read halo (the
-// FP64 sweep moves 2.06x its algorithmic bytes on 16 x 8 tiles), 511^3:
-// 8.42 against 9.39 ms per sweep (48 x 10: 8.77 ms).
-template <int X_, int Y_, int Z_, int T_, int E_> struct Tile {
-    static constexpr int X = X_, Y = Y_, Z = Z_, T = T_, E = E_;
+// Tiles (X, Y: column; T: threads, at least one per point of the plane with
+// its halo, so that no wave does a second round of a stage while the others
+// wait at its barrier; E: waves per SIMD to fit in registers).
+//  - 64 x 11 (68 x 15 = 1020 points), FP32, 18 LDS planes = 74 KB, two
+//    workgroups per CU: a row of 68 values touches 4 lines of 128 bytes for
+//    the 2 it owns, one of 36 values 3 for 1, and the neighbours' lines are
+//    the traffic that binds large grids.  511^3: 3.72 ms per sweep, 32 x 16
+//    3.91, 48 x 10 3.80; 255^3: 0.464, 0.495, 0.521 ms.
+//  - 32 x 16 (36 x 20 = 720 points), which fills the last round of
+//    workgroups better on middle grids (127^3: 54 us, 64 x 11 65 us); with a
+//    per-cell G the FP32 tile for all large grids (64 x 11 would need more
+//    than half the LDS then).  FP64: one workgroup of 105 KB and 12 waves per
+//    CU; 48 x 15 and 32 x 24 with 1024 threads are no faster (255^3: 0.81 ms
+//    against 0.90 and 0.91).
+//  - 16 x 8 (20 x 12 = 240 points), for grids that would leave most CUs
+//    without work: its march step takes 1.5 us on an otherwise idle CU, that
+//    of the larger tiles 2.5 to 3.5 us (63^3 FP32: 18.5 us, 32 x 16 21 us).
+template <int X_, int Y_, int T_, int E_> struct Tile {
+    static constexpr int X = X_, Y = Y_, T = T_, E = E_;
 };
-using TileF_wide = Tile<48, 10, 32, 768, 6>;
-using TileF_square = Tile<32, 16, 32, 768, 6>;
-using TileD = Tile<32, 16, 32, 768, 3>;
+using TileF_wide = Tile<64, 11, 1024, 8>;
+using TileF_square = Tile<32, 16, 768, 6>;
+using TileF_small = Tile<16, 8, 256, 6>;
+using TileD_square = Tile<32, 16, 768, 3>;
+using TileD_small = Tile<16, 8, 256, 3>;
+enum { TILE_WIDE = 0, TILE_SQUARE, TILE_SMALL };
 
 // first and one-past-last tile index along an axis whose tiles lie strictly
 // inside with their 2-point halo: 3 <= i0 and i0 + T + 2 <= n
@@ -521,28 +503,45 @@ inline void interior_range(int n, int T, int nb, int& b0, int& b1)
     if (b1 < b0) b1 = b0;
 }
 
-template <typename S>
-long tile_count(int nx, int ny, int nz)
-{
-    return (long)((nx + S::X - 1) / S::X) * ((ny + S::Y - 1) / S::Y) * ((nz + S::Z - 1) / S::Z);
-}
-
-template <typename S, typename R, int MODE>
+template <typename S, typename R, int MODE, bool G = true>
 void run_3d(const SweepArgs<R>& a, hipStream_t s)
 {
-    constexpr int TX = S::X, TY = S::Y, ZC = S::Z, NT = S::T, WPE = S::E;
+    constexpr int TX = S::X, TY = S::Y, NT = S::T, WPE = S::E;
     TileSet ts;
+    ts.zc = a.plan.zc;
     ts.nbx = (a.nx + TX - 1) / TX;
     ts.nby = (a.ny + TY - 1) / TY;
-    ts.nbz = (a.nz + ZC - 1) / ZC;
+    ts.nbz = (a.nz + ts.zc - 1) / ts.zc;
     interior_range(a.nx, TX, ts.nbx, ts.bx0, ts.bx1);
     interior_range(a.ny, TY, ts.nby, ts.by0, ts.by1);
     const int nb = ts.nbx * ts.nby * ts.nbz;
-    if (a.igdc) k_fused_3d<R, TX, TY, ZC, MODE, NT, WPE, true><<<nb, NT, 0, s>>>(a, ts);
-    else k_fused_3d<R, TX, TY, ZC, MODE, NT, WPE, false><<<nb, NT, 0, s>>>(a, ts);
+    auto go = [&](auto hg, auto frz) {
+        k_fused_3d<R, TX, TY, MODE, NT, WPE, decltype(hg)::value, decltype(frz)::value><<<nb, NT, 0, s>>>(a, ts);
+    };
+    const bool frz = a.lam_mode == LAM_FROZEN;
+    if constexpr (G) {
+        if (a.igdc) {
+            frz ? go(std::true_type{}, std::true_type{}) : go(std::true_type{}, std::false_type{});
+            return;
+        }
+    }
+    frz ? go(std::false_type{}, std::true_type{}) : go(std::false_type{}, std::false_type{});
 }
 
-// Compute units of the current device (two FP32 workgroups run on each).
+template <typename R, int MODE>
+void run_3d(const SweepArgs<R>& a, hipStream_t s)
+{
+    if constexpr (sizeof(R) == 8) {
+        if (a.plan.tile == TILE_SMALL) run_3d<TileD_small, R, MODE>(a, s);
+        else run_3d<TileD_square, R, MODE>(a, s);
+    } else {
+        if (a.plan.tile == TILE_SMALL) run_3d<TileF_small, R, MODE>(a, s);
+        else if (a.plan.tile == TILE_WIDE) run_3d<TileF_wide, R, MODE, false>(a, s);
+        else run_3d<TileF_square, R, MODE>(a, s);
+    }
+}
+
+// Compute units of the current device.
 int device_cus()
 {
     int dev = 0, n = 0;
@@ -553,31 +552,72 @@ int device_cus()
     return n;
 }
 
-// FP32 tile shape of a grid: rounds of resident workgroups times the cost of
-// a round, a 48 x 10 round costing 0.85 of a 32 x 16 one (measured at 511^3:
-// 18 rounds in 4.10 ms against 16 in 4.30 ms).
-bool wide_tile(int nx, int ny, int nz)
-{
-    static const int resident = 2 * device_cus();
-    const long rw = (tile_count<TileF_wide>(nx, ny, nz) + resident - 1) / resident;
-    const long rs = (tile_count<TileF_square>(nx, ny, nz) + resident - 1) / resident;
-    return 0.85 * (double)rw <= (double)rs;
-}
-
-template <typename R, int MODE>
-void run_3d(const SweepArgs<R>& a, hipStream_t s)
-{
-    if constexpr (sizeof(R) == 8) run_3d<TileD, R, MODE>(a, s);
-    else if (wide_tile(a.nx, a.ny, a.nz)) run_3d<TileF_wide, R, MODE>(a, s);
-    else run_3d<TileF_square, R, MODE>(a, s);
-}
-
+// What a sweep with a tile costs, in us: a march step of a workgroup alone
+// on its CU, of a full round of `res` workgroups per CU, and the launch with
+// the fill of the pipeline.
+struct TileCost {
+    int tile, x, y, res;
+    double alone, full, launch;
+};
+const TileCost kCost32[] = {{TILE_WIDE, 64, 11, 2, 3.5, 6.0, 5.0}, {TILE_SQUARE, 32, 16, 2, 2.61, 5.23, 5.0},
+                            {TILE_SMALL, 16, 8, 8, 1.5, 5.8, 2.0}};
+const TileCost kCost64[] = {{TILE_SQUARE, 32, 16, 1, 3.0, 3.3, 5.0}, {TILE_SMALL, 16, 8, 4, 1.9, 4.2, 2.0}};
 
 }  // namespace
 
-// Measured on MI355X at 255^3: fused 0.55 ms (FP32) and 1.14 ms (FP64) per
+// Measured on MI355X at 255^3: fused 0.46 ms (FP32) and 0.81 ms (FP64) per
 // sweep against 1.57 ms for the three unfused FP64 kernels.
 bool fused_preferred(int, bool) { return true; }
+
+// Tile and chunk length of a grid.  A workgroup marches zc + 3 planes one
+// after the other, so short chunks cut the latency of a sweep where the
+// chip has room for more workgroups (63^3: 18 us in chunks of 4 planes, 58 us
+// in chunks of 32), and long ones the planes that are loaded and computed
+// twice.  In between the rounds of resident workgroups decide: the rule
+// takes the least modelled time.  The costs above, the share of the last
+// round that overlaps the one before and the cost of long marches (the
+// workgroups of an XCD drift apart in z and lose the halo lines they share
+// in its L2: FP32 511^3 3.72 ms in chunks of 16 planes, 3.99 in 64) were
+// fitted to sweeps timed on 28 grids from 20^3 to 511^3 with every tile and
+// chunk length: the choice is within 4 % (FP32) and 6 % (FP64) of the best
+// of them, 1 % on average.  FP64 chunks of 64 planes only where a plane has
+// at most 1 MB: 255^3 0.81 against 0.85 ms in chunks of 32, but 511^3 7.75
+// against 6.59 ms in chunks of 43.
+FusedPlan fused_plan_3d(bool fp32, bool has_g, int nx, int ny, int nz, long sz)
+{
+    static const int cus = device_cus();
+    static const int kChunks[] = {3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 28, 32, 43, 50, 64};
+    const double drift = fp32 ? 120.0 : 1000.0, overlap = fp32 ? 0.65 : 0.19;
+    const double plane = (double)sz * (fp32 ? 4.0 : 8.0);
+    FusedPlan best{0, 0};
+    double t_best = INFINITY;
+    const TileCost* c = fp32 ? kCost32 : kCost64;
+    for (int q = 0; q < (fp32 ? 3 : 2); ++q) {
+        if (has_g && c[q].tile == TILE_WIDE) continue;
+        const double columns = (double)((nx + c[q].x - 1) / c[q].x) * ((ny + c[q].y - 1) / c[q].y);
+        for (int zc : kChunks) {
+            // the planes of a chunk within the range of 32-bit offsets, the
+            // workgroups within that of a launch
+            const double nb = columns * ((nz + zc - 1) / zc);
+            if ((zc + 8) * plane > 2147483647.0 || nb * c[q].x * c[q].y > 2147483647.0) continue;
+            if (!fp32 && zc > 50 && plane > 1048576.0) continue;
+            const double rounds = std::floor(nb / (cus * c[q].res)), rest = nb - rounds * cus * c[q].res;
+            double step = rounds * c[q].full * (1.0 + zc / drift);
+            if (rest > 0.0) {
+                const double m = std::ceil(rest / cus);
+                double last = c[q].res > 1 ? c[q].alone + (c[q].full - c[q].alone) * (m - 1.0) / (c[q].res - 1.0) : c[q].full;
+                if (rounds > 0.0) last = last * (1.0 - overlap) + c[q].full * overlap * rest / (cus * c[q].res);
+                step += last;
+            }
+            const double t = c[q].launch + (zc + 3) * step;
+            if (t < t_best) {
+                t_best = t;
+                best = FusedPlan{c[q].tile, zc};
+            }
+        }
+    }
+    return best;
+}
 
 template <typename R>
 void launch_sweep_fused_3d(const SweepArgs<R>& a, int mode, hipStream_t s)

@@ -374,14 +374,17 @@ int ep_batch_init(int n, const ep_params* p, const double* const* cohesion, void
                   void* stream, ep_batch** out);
 
 /* Autotuner: picks the tile shape of each model size (models with equal
- * nx, ny share one) by timing `reps` batched sweeps of all models per
+ * nx, ny share one) by timing 6 * `reps` batched sweeps of all models per
  * candidate, coordinate descent over the size classes; FP32-field batches
  * get a second shape per size for their FP64 finishing sweeps, tuned the
  * same way.  The timed sweeps leave the state unchanged.  Optional; the
  * default shape is 64 x 8. */
 int ep_batch_tune(ep_batch* b, int reps);
 
-/* Tile shape used for model i. */
+/* Tile shape of model i: the points that one pass of a workgroup's threads
+ * covers.  A workgroup makes several passes over its tile and its halo and
+ * several sweeps per launch; while few models are left, the batch uses
+ * shapes for few tiles instead. */
 int ep_batch_tile_shape(const ep_batch* b, int i, int* tx, int* ty);
 
 /* One load increment of every model; st: n entries (required), filled as by

@@ -128,13 +128,8 @@ size_t carve(const ep_params* p, ep_handle* h, char* base)
         if (h) h->vguess64[d] = (double*)q;
     }
     if (p->ndim == 2) {
-        const long nt = (long)((nx + kBatchTiles[SINGLE_SHAPE][0] - 1) / kBatchTiles[SINGLE_SHAPE][0]) *
-                        ((ny + kBatchTiles[SINGLE_SHAPE][1] - 1) / kBatchTiles[SINGLE_SHAPE][1]);
         q = take(10 * sizeof(SweepArgs<double>)); if (h) h->tab64 = (SweepArgs<double>*)q;
         q = take(6 * sizeof(SweepArgs<float>)); if (h) h->tab32 = (SweepArgs<float>*)q;
-        q = take(nt * sizeof(TileRef)); if (h) h->tiles = (TileRef*)q;
-        q = take(sizeof(int)); if (h) h->tcount = (int*)q;
-        if (h) h->ntiles = nt;
     }
     if (h) {
         h->sy = (int)sy;
@@ -276,22 +271,45 @@ SweepArgs<float> args32(const ep_handle* h, int from)
     return make_args<float>(h, h->it32[from], h->it32[1 - from], h->old32, h->coh32, h->lam32, false);
 }
 
-// One PT sweep reading buffer `from` (physical: pseudo-time terms removed;
-// lam_mode: LAM_*, 2D tile sweeps only).  2D fused sweeps run the batched
-// tile kernel on this model's own one-entry table and tile list, so that a
-// model gives bitwise the same iterates alone and inside a batch.
+// Launch of ns sweeps of a 2D model with its own tile shape.
+Launch2d launch_2d(const ep_handle* h, bool fp32, int mode, int ns)
+{
+    Launch2d l;
+    l.shape = h->shape2[fp32];
+    l.mode = mode;
+    l.ns = ns;
+    const int tx = mode == MODE_PHYS ? PHYS_TILE : kTiles2d[fp32][l.shape].tx;
+    const int ty = mode == MODE_PHYS ? PHYS_TILE : kTiles2d[fp32][l.shape].ty;
+    l.nbx = (h->nx + tx - 1) / tx;
+    l.tiles = (int)std::min<long>((long)l.nbx * ((h->ny + ty - 1) / ty), INT_MAX);
+    l.grid = std::min(l.tiles, h->grid2[fp32]);
+    l.has_g = h->has_g;
+    return l;
+}
+
+// Sweeps a launch can do in this precision.
+int sweeps_per_launch(const ep_handle* h, bool fp32)
+{
+    const bool fused = fp32 ? h->fused32 : h->fused64;
+    return h->ndim == 2 && fused ? kTiles2d[fp32][h->shape2[fp32]].k : 1;
+}
+
+// ns PT sweeps reading buffer `from` (physical: pseudo-time terms removed;
+// lam_mode: LAM_* of the first; ns > 1 only up to sweeps_per_launch).  2D
+// fused sweeps run the batched tile kernel on this model's own one-entry
+// table, so that a model gives bitwise the same iterates alone and inside a
+// batch.
 template <typename R>
-void launch_sweep(const ep_handle* h, bool physical, int from, int mode, int lam_mode = LAM_COMPUTE)
+void launch_sweep(const ep_handle* h, bool physical, int from, int mode, int lam_mode = LAM_COMPUTE, int ns = 1)
 {
     const bool fused = sizeof(R) == 4 ? h->fused32 : h->fused64;
     if (h->ndim == 2 && fused) {
-        if (sizeof(R) == 4)
-            launch_sweep_batch_2d<float>(SINGLE_SHAPE, h->tab32 + 2 * lam_mode + from, h->tiles, h->tcount, mode,
-                                         h->grid2[1], h->st);
+        const Launch2d l = launch_2d(h, sizeof(R) == 4, mode, ns);
+        if constexpr (sizeof(R) == 4)
+            launch_sweep_batch_2d<float>(h->tab32 + 2 * lam_mode + from, nullptr, nullptr, l, h->st);
         else
-            launch_sweep_batch_2d<double>(SINGLE_SHAPE,
-                                          h->tab64 + (physical ? 6 + 2 * (lam_mode == LAM_FROZEN) : 2 * lam_mode) + from,
-                                          h->tiles, h->tcount, mode, h->grid2[0], h->st);
+            launch_sweep_batch_2d<double>(
+                h->tab64 + (physical ? 6 + 2 * (lam_mode == LAM_FROZEN) : 2 * lam_mode) + from, nullptr, nullptr, l, h->st);
         return;
     }
     SweepArgs<R> a;
@@ -308,7 +326,6 @@ void launch_sweep(const ep_handle* h, bool physical, int from, int mode, int lam
 
 // Device tables of the 2D tile kernel: FP64 [lam mode][from], then physical
 // [from] and physical with the frozen Lambda [from]; FP32 [lam mode][from].
-// The tile list (shape 0) is written once.
 int upload_tables(ep_handle* h)
 {
     if (h->ndim != 2) return EP_OK;
@@ -417,14 +434,15 @@ int run_batch(ep_handle* h, bool use32, int nb, bool check_last)
 {
     if (h->timing) HIPCHK(h, hipEventRecord(h->ev0, h->st));
     launch_reset_red(h->red, h->st);
-    for (int b = 0; b < nb; ++b) {
-        int mode = (check_last && b == nb - 1) ? MODE_CHECK : MODE_UPDATE;
+    for (int b = 0, k = sweeps_per_launch(h, use32); b < nb; b += k) {
+        const int ns = std::min(k, nb - b);
+        const int mode = (check_last && b + ns == nb) ? MODE_CHECK : MODE_UPDATE;
         const int lm = sweep_lam_mode(h, b);
         if (use32) {
-            launch_sweep<float>(h, false, h->cur32, mode, lm);
+            launch_sweep<float>(h, false, h->cur32, mode, lm, ns);
             h->cur32 = 1 - h->cur32;
         } else {
-            launch_sweep<double>(h, false, h->cur64, mode, lm);
+            launch_sweep<double>(h, false, h->cur64, mode, lm, ns);
             h->cur64 = 1 - h->cur64;
         }
     }
@@ -869,23 +887,13 @@ int handle_create(const ep_params* p, const double* cohesion, char* d_workspace,
     h->it32_valid = false;
     h->old32_valid = false;
     if (h->ndim == 2) {
-        // tile list of the whole model and the persistent grid sizes
-        const int tx = kBatchTiles[SINGLE_SHAPE][0], ty = kBatchTiles[SINGLE_SHAPE][1];
-        const int nbx = (h->nx + tx - 1) / tx;
-        std::vector<TileRef> tl(h->ntiles);
-        for (long t = 0; t < h->ntiles; ++t) tl[t] = TileRef{0, (short)(t % nbx), (short)(t / nbx)};
-        const int cnt = (int)h->ntiles;
-        if (hipMemcpyAsync(h->tiles, tl.data(), tl.size() * sizeof(TileRef), hipMemcpyHostToDevice, h->st) !=
-                hipSuccess ||
-            hipMemcpyAsync(h->tcount, &cnt, sizeof(int), hipMemcpyHostToDevice, h->st) != hipSuccess ||
-            hipStreamSynchronize(h->st) != hipSuccess)
-            return fail(EP_EDEVICE);
+        // tile shapes and the persistent grid sizes
         int ncu = 0;
         if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, 0) != hipSuccess || ncu <= 0) ncu = 256;
-        h->grid2[0] =
-            (int)std::min<long>(h->ntiles, (long)ncu * std::min(8, batch_blocks_per_cu<double>(SINGLE_SHAPE)));
-        h->grid2[1] =
-            (int)std::min<long>(h->ntiles, (long)ncu * std::min(8, batch_blocks_per_cu<float>(SINGLE_SHAPE)));
+        for (int q = 0; q < 2; ++q) {
+            const int sh = h->shape2[q] = tile2d_choice(q == 1, h->nx, h->ny, ncu);
+            h->grid2[q] = ncu * std::min(8, q ? batch_blocks_per_cu<float>(sh) : batch_blocks_per_cu<double>(sh));
+        }
         if (upload_tables(h) != EP_OK) return fail(EP_EDEVICE);
     }
     if (hipGetLastError() != hipSuccess) return fail(EP_EDEVICE);
@@ -909,12 +917,12 @@ constexpr size_t NOALLOC_SCRATCH_BYTES = 64 * 1024;
 static __device__ __align__(256) unsigned char scratch[NOALLOC_SCRATCH_BYTES];
 
 // Layout: reduction counters, then two FP64 argument tables (PT and physical
-// evaluation), then the tile count and the tile list (2D models).
+// evaluation).  2D models of more than 8,000 tiles of 64 x 16 cells are
+// refused (the interface's stated limit).
 constexpr size_t NA_RED = 0;
 constexpr size_t NA_TAB = 256;
-constexpr size_t NA_CNT = NA_TAB + (2 * sizeof(SweepArgs<double>) + 255) / 256 * 256;
-constexpr size_t NA_TILES = NA_CNT + 256;
-constexpr long NOALLOC_MAX_TILES = (long)((NOALLOC_SCRATCH_BYTES - NA_TILES) / sizeof(TileRef));
+constexpr long NOALLOC_MAX_TILES = 8000;
+static_assert(NA_TAB + 2 * sizeof(SweepArgs<double>) <= NOALLOC_SCRATCH_BYTES, "the tables fit");
 
 // Device address of `scratch` on the current device, looked up once per device.
 int noalloc_scratch(ep_handle* h, char** out)
@@ -1048,27 +1056,23 @@ int ep_residual_noalloc(ep_handle* h, ep_residual_info* r)
     int rc;
     if ((rc = noalloc_scratch(h, &base))) return rc;
     const bool tiles2d = h->ndim == 2 && h->fused64;
-    if (tiles2d && h->ntiles > NOALLOC_MAX_TILES)
+    const long ntiles = (long)((h->nx + 63) / 64) * ((h->ny + 15) / 16);
+    if (tiles2d && ntiles > NOALLOC_MAX_TILES)
         return set_err(h, EP_EINVAL, "ep_residual_noalloc: %ld tiles exceed the scratch capacity of %ld (%zu bytes)",
-                       h->ntiles, NOALLOC_MAX_TILES, NOALLOC_SCRATCH_BYTES);
+                       ntiles, NOALLOC_MAX_TILES, NOALLOC_SCRATCH_BYTES);
     ensure_it64(h);
     auto* red = (unsigned long long*)(base + NA_RED);
     auto* tab = (SweepArgs<double>*)(base + NA_TAB);
-    auto* cnt = (int*)(base + NA_CNT);
-    auto* tiles = (TileRef*)(base + NA_TILES);
     SweepArgs<double> a[2] = {args64(h, false, h->cur64), args64(h, true, h->cur64)};
     for (auto& x : a) x.red = red;
     if (tiles2d) {
-        // stage the two argument tables and this model's tile list
-        const int n = (int)h->ntiles;
+        // stage the two argument tables
         HIPCHK(h, hipMemcpyAsync(tab, a, sizeof(a), hipMemcpyHostToDevice, h->st));
-        HIPCHK(h, hipMemcpyAsync(cnt, &n, sizeof(int), hipMemcpyHostToDevice, h->st));
-        HIPCHK(h, hipMemcpyAsync(tiles, h->tiles, h->ntiles * sizeof(TileRef), hipMemcpyDeviceToDevice, h->st));
         HIPCHK(h, hipStreamSynchronize(h->st));          // the host tables leave scope
     }
     auto sweep = [&](int q, int mode) {
         if (tiles2d)
-            launch_sweep_batch_2d<double>(SINGLE_SHAPE, tab + q, tiles, cnt, mode, h->grid2[0], h->st);
+            launch_sweep_batch_2d<double>(tab + q, nullptr, nullptr, launch_2d(h, false, mode, 1), h->st);
         else if (h->ndim == 2)
             launch_sweep_unfused_2d<double>(a[q], mode, h->st);
         else if (h->fused64 && a[q].fs > 0 && a[q].plan.zc > 0)

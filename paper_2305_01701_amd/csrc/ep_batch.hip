@@ -4,7 +4,7 @@
 // Every model is an ordinary solver handle carved from the batch workspace,
 // so prologue, precision conversions, epilogue and field I/O are the
 // single-model code.  What is shared is the PT iteration: a graph of n_check
-// sweeps (a reduction reset, then per sweep one persistent launch per
+// sweeps (a reduction reset, then persistent launches of up to K sweeps per
 // precision and tile shape in use, the last sweep with the residual check)
 // is captured on first use and replayed; each launch walks a device tile list of the
 // models still iterating in that precision.  After a replay the host reads
@@ -40,6 +40,7 @@ struct ep_batch {
     std::vector<long> cells;
     std::vector<int> shape;             // tile shape per model (sweeps in the batch precision)
     std::vector<int> shape64;           // FP32-field batches: tile shape of the FP64 finishing sweeps
+    int ncu;
     unsigned long long* red;            // n x RED_N
     double* cols;                       // n x 4
     SweepArgs<double>* tab64;           // 2 x n (parity of the ping-pong buffers)
@@ -88,12 +89,6 @@ size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
 int resolved_check(const ep_params& p) { return p.n_check > 0 ? p.n_check : (p.ndim == 3 ? 10 : 100); }
 
-long tiles_of(const ep_params& p, int s)
-{
-    const int tx = kBatchTiles[s][0], ty = kBatchTiles[s][1];
-    return (long)((p.nx + tx - 1) / tx) * ((p.ny + ty - 1) / ty);
-}
-
 int validate_batch(int n, const ep_params* p)
 {
     if (n <= 0 || !p) return EP_EINVAL;
@@ -131,7 +126,7 @@ BatchLayout layout(int n, const ep_params* p)
         for (int s = 0; s < BATCH_SHAPES; ++s) {
             long c = 0;
             if (q == 0 || fp32)
-                for (int i = 0; i < n; ++i) c += tiles_of(p[i], s);
+                for (int i = 0; i < n; ++i) c += tiles2d(q == 1, s, p[i].nx, p[i].ny);
             L.lists[q][s] = take((size_t)std::max(c, 1L) * sizeof(TileRef));
         }
     L.cnt = take(2 * BATCH_SHAPES * sizeof(int));
@@ -163,28 +158,50 @@ void fill_tables(ep_batch* b)
 
 // Tile lists of the running models (precision of each model's current
 // sweeps), or of all models when all_models is set, in FP32 when all32 (the
-// batch precision) else in FP64.
+// batch precision) else in FP64.  Running models of a precision take their
+// (tuned) shapes, or together one of the others where the launch then has
+// less modelled time: the shapes for few tiles once few models are left.
 void fill_lists(ep_batch* b, bool all_models, bool all32 = true)
 {
     for (int q = 0; q < 2; ++q)
         for (int s = 0; s < BATCH_SHAPES; ++s) b->h_list[q][s].clear();
     b->cs32 = b->cs64 = 0;
-    for (int i = 0; i < b->n; ++i) {
-        ep_handle* h = b->m[i];
-        bool use32;
-        if (all_models) {
-            use32 = b->fp32 && all32;
-        } else {
-            if (!h->ctl.running) continue;
-            use32 = h->ctl.use32;
+    auto active = [&](int i, int q) {
+        if (all_models) return (b->fp32 && all32) == (q == 1);
+        return b->m[i]->ctl.running && b->m[i]->ctl.use32 == (q == 1);
+    };
+    auto own_shape = [&](int i, int q) { return (q == 1 || !b->fp32) ? b->shape[i] : b->shape64[i]; };
+    for (int q = 0; q < 2; ++q) {
+        int common = -1;
+        if (!all_models) {
+            long own[BATCH_SHAPES] = {};
+            double t_own = 0;
+            for (int i = 0; i < b->n; ++i)
+                if (active(i, q)) own[own_shape(i, q)] += tiles2d(q == 1, own_shape(i, q), b->m[i]->nx, b->m[i]->ny);
+            for (int s = 0; s < BATCH_SHAPES; ++s)
+                if (own[s] > 0) t_own += tile2d_cost(q == 1, s, own[s], b->ncu);
+            for (int s = TUNED_SHAPES; s < BATCH_SHAPES; ++s) {
+                long tiles = 0;
+                for (int i = 0; i < b->n; ++i)
+                    if (active(i, q)) tiles += tiles2d(q == 1, s, b->m[i]->nx, b->m[i]->ny);
+                const double t = tile2d_cost(q == 1, s, tiles, b->ncu);
+                if (tiles > 0 && t < t_own) {
+                    t_own = t;
+                    common = s;
+                }
+            }
         }
-        const int s = (use32 || !b->fp32) ? b->shape[i] : b->shape64[i];
-        const int tx = kBatchTiles[s][0], ty = kBatchTiles[s][1];
-        const int nbx = (h->nx + tx - 1) / tx, nby = (h->ny + ty - 1) / ty;
-        auto& L = b->h_list[use32 ? 1 : 0][s];
-        for (int by = 0; by < nby; ++by)
-            for (int bx = 0; bx < nbx; ++bx) L.push_back(TileRef{i, (short)bx, (short)by});
-        (use32 ? b->cs32 : b->cs64) += (double)b->cells[i] * b->n_check;
+        for (int i = 0; i < b->n; ++i) {
+            if (!active(i, q)) continue;
+            ep_handle* h = b->m[i];
+            const int s = common >= 0 ? common : own_shape(i, q);
+            const int tx = kTiles2d[q][s].tx, ty = kTiles2d[q][s].ty;
+            const int nbx = (h->nx + tx - 1) / tx, nby = (h->ny + ty - 1) / ty;
+            auto& L = b->h_list[q][s];
+            for (int by = 0; by < nby; ++by)
+                for (int bx = 0; bx < nbx; ++bx) L.push_back(TileRef{i, bx, by});
+            (q == 1 ? b->cs32 : b->cs64) += (double)b->cells[i] * b->n_check;
+        }
     }
     for (int q = 0; q < 2; ++q)
         for (int s = 0; s < BATCH_SHAPES; ++s) b->h_cnt[q * BATCH_SHAPES + s] = (int)b->h_list[q][s].size();
@@ -208,13 +225,6 @@ int upload(ep_batch* b)
     return EP_OK;
 }
 
-bool shape_used(const ep_batch* b, int s)
-{
-    for (int i = 0; i < b->n; ++i)
-        if (b->shape[i] == s || b->shape64[i] == s) return true;
-    return false;
-}
-
 // Bit q * BATCH_SHAPES + shape for every non-empty tile list (q: 0 FP64, 1 FP32).
 unsigned list_mask(const ep_batch* b)
 {
@@ -225,25 +235,34 @@ unsigned list_mask(const ep_batch* b)
     return m;
 }
 
-// nsw sweeps of every tile in the lists selected by mask; the last one in
-// CHECK mode when check is set.  With alternate, the sweeps advance the
-// iteration (ping-pong); without, every sweep reads the current buffers and
-// writes the other ones (timing runs that leave the state unchanged).
+// nsw sweeps of every tile in the lists selected by mask, in launches of at
+// most K sweeps of the list's shape; the last one in CHECK mode when check is
+// set.  With alternate, the launches advance the iteration (ping-pong), an
+// even number of them, so that every model's current buffer stays in place;
+// without, every launch reads the current buffers and writes the other ones
+// (timing runs that leave the state unchanged).
 void enqueue_sweeps(ep_batch* b, int nsw, bool check, bool reset, bool alternate, unsigned mask, hipStream_t s)
 {
     if (reset) launch_reset_red_n(b->red, b->n, s);
-    for (int k = 0; k < nsw; ++k) {
-        const int mode = (check && k == nsw - 1) ? MODE_CHECK : MODE_UPDATE;
-        const int slot = !alternate ? 1 : k == 0 ? 0 : (k & 1) ? 2 : 1;
+    for (int q = 1; q >= 0; --q)
         for (int sh = 0; sh < BATCH_SHAPES; ++sh) {
-            if (b->fp32 && (mask >> (BATCH_SHAPES + sh) & 1u))
-                launch_sweep_batch_2d<float>(sh, b->tab32 + slot * b->n, b->list[1][sh], b->cnt + BATCH_SHAPES + sh,
-                                             mode, b->grid[1][sh], s);
-            if (mask >> sh & 1u)
-                launch_sweep_batch_2d<double>(sh, b->tab64 + slot * b->n, b->list[0][sh], b->cnt + sh, mode,
-                                              b->grid[0][sh], s);
+            if (!(mask >> (q * BATCH_SHAPES + sh) & 1u)) continue;
+            const int k = kTiles2d[q][sh].k;
+            int n = (nsw + k - 1) / k;
+            if (alternate && n % 2 != 0) ++n;
+            Launch2d l{};
+            l.shape = sh;
+            l.grid = b->grid[q][sh];
+            l.nbx = 1;
+            for (int c = 0; c < n; ++c) {
+                l.ns = nsw / n + (c < nsw % n ? 1 : 0);
+                l.mode = (check && c == n - 1) ? MODE_CHECK : MODE_UPDATE;
+                const int slot = !alternate ? 1 : c == 0 ? 0 : (c & 1) ? 2 : 1;
+                const int* cnt = b->cnt + q * BATCH_SHAPES + sh;
+                if (q == 1) launch_sweep_batch_2d<float>(b->tab32 + slot * b->n, b->list[1][sh], cnt, l, s);
+                else launch_sweep_batch_2d<double>(b->tab64 + slot * b->n, b->list[0][sh], cnt, l, s);
+            }
         }
-    }
 }
 
 void drop_graphs(ep_batch* b)
@@ -352,10 +371,11 @@ int ep_batch_init(int n, const ep_params* p, const double* const* cohesion, void
         b->m.push_back(h);
         b->cells.push_back((long)p[i].nx * p[i].ny);
         b->shape.push_back(0);
-        b->shape64.push_back(0);
+        b->shape64.push_back(5);        // 24 x 24 cells, K = 2: 20 us per FP64 sweep of 777 x 1010 cells, shape 0 22
     }
     int ncu = 0;
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, 0) != hipSuccess || ncu <= 0) ncu = 256;
+    b->ncu = ncu;
     for (int s = 0; s < BATCH_SHAPES; ++s) {
         b->grid[0][s] = ncu * std::min(8, batch_blocks_per_cu<double>(s));
         b->grid[1][s] = ncu * std::min(8, batch_blocks_per_cu<float>(s));
@@ -385,8 +405,8 @@ ep_handle* ep_batch_model(ep_batch* b, int i)
 int ep_batch_tile_shape(const ep_batch* b, int i, int* tx, int* ty)
 {
     if (!b || i < 0 || i >= b->n) return EP_EINVAL;
-    if (tx) *tx = kBatchTiles[b->shape[i]][0];
-    if (ty) *ty = kBatchTiles[b->shape[i]][1];
+    if (tx) *tx = kTiles2d[b->fp32][b->shape[i]].pass_x;
+    if (ty) *ty = kTiles2d[b->fp32][b->shape[i]].pass_y;
     return EP_OK;
 }
 
@@ -410,9 +430,10 @@ int ep_batch_tune(ep_batch* b, int reps)
             int rc = upload(b);
             if (rc) return rc;
             const unsigned mask = list_mask(b);
-            enqueue_sweeps(b, 1, false, false, false, mask, b->st);    // warm-up
+            // whole launches of the shapes with two and with three sweeps
+            enqueue_sweeps(b, 6, false, false, false, mask, b->st);    // warm-up
             BCHK(b, hipEventRecord(b->ev0, b->st));
-            enqueue_sweeps(b, reps, false, false, false, mask, b->st);
+            enqueue_sweeps(b, 6 * reps, false, false, false, mask, b->st);
             BCHK(b, hipEventRecord(b->ev1, b->st));
             BCHK(b, hipEventSynchronize(b->ev1));
             BCHK(b, hipGetLastError());
@@ -428,7 +449,7 @@ int ep_batch_tune(ep_batch* b, int reps)
             for (auto& cl : classes) {
                 const int keep = shape[cl.second[0]];
                 int best_s = keep;
-                for (int s = 0; s < BATCH_SHAPES; ++s) {
+                for (int s = 0; s < TUNED_SHAPES; ++s) {
                     if (s == keep) continue;
                     for (int i : cl.second) shape[i] = s;
                     double t;

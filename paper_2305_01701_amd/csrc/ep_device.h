@@ -151,6 +151,33 @@ __device__ __forceinline__ double fast_rcp(double x) { return 1.0 / x; }
 __device__ __forceinline__ float fast_sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
 __device__ __forceinline__ double fast_sqrt(double x) { return sqrt(x); }
 
+// x / 3, correctly rounded, by Markstein's theorem: with z the rounded 1/3
+// the product x z is within one unit in the last place of x / 3, so one
+// residual step rounds to the quotient (3 operations instead of the 10 of a
+// division).
+__device__ __forceinline__ float third(float x)
+{
+    const float z = 1.0f / 3.0f, q = x * z;
+    return __builtin_fmaf(__builtin_fmaf(-3.0f, q, x), z, q);
+}
+__device__ __forceinline__ double third(double x)
+{
+    const double z = 1.0 / 3.0, q = x * z;
+    return __builtin_fma(__builtin_fma(-3.0, q, x), z, q);
+}
+
+// 1 / (D + lam) with invD = 1 / D at hand: the FP64 division (about 12
+// instructions) is left out where no lane of the wave yields; it gives the
+// same bits for lam = 0.
+template <typename R>
+__device__ __forceinline__ R rcp_sum(R D, R lam, R invD)
+{
+    if constexpr (sizeof(R) == 8) {
+        if (!__any(lam != R(0))) return invD;
+    }
+    return fast_rcp(D + lam);
+}
+
 // Return mapping at a centre (the return-mapping section, Lambda form on the
 // staggered grid).  The deviator of the iteration is tau = T / (D + Lambda)
 // with T = tau_k/(G~ dtau) + S, S = tau^/(G dt) + 2 e' the physical trial,
@@ -176,6 +203,11 @@ __device__ __forceinline__ R centre_return(R nT2, R nS2, R sh2, R Dp, R invDp, R
 #pragma clang fp contract(on)   // same rounding in every kernel that inlines it
     R Y0 = A * p + B * c;
     Y0 = Y0 > R(0) ? Y0 : R(0);
+    if constexpr (sizeof(R) == 8) {
+        // no lane near the bound: elastic without the FP64 square root
+        const R bound = Y0 * Dp;
+        if (!__any(nS2 + sh2 >= bound * bound * R(1.0 - 1e-12))) return R(0);
+    }
     const R sqS = fast_sqrt(nS2 + sh2);
     if (!(sqS * invDp > Y0)) return R(0);
     const R ptr = p;

@@ -62,13 +62,11 @@ struct ep_handle {
     long t_n[2];
     std::vector<double> hist_r;
     std::vector<int> hist_p;
-    // 2D: tables and tile list of the tile kernel (one model, tile shape 0)
+    // 2D: argument tables of the tile kernel, [FP64, FP32] tile shape and
+    // resident workgroups of this model
     ep::SweepArgs<double>* tab64;
     ep::SweepArgs<float>* tab32;
-    ep::TileRef* tiles;
-    int* tcount;
-    long ntiles;
-    int grid2[2];
+    int shape2[2], grid2[2];
     ep::StepCtl ctl;
     double* vguess64[3];   // 3D: velocities of a supplied starting guess
     bool guess_ready;      // the next increment tries vguess64

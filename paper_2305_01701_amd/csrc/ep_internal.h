@@ -84,20 +84,42 @@ FusedPlan fused_plan_3d(bool fp32, bool has_g, int nx, int ny, int nz, long sz);
 // Whether the automatic choice uses the fused sweep for this case.
 bool fused_preferred(int ndim, bool fp32);
 
-// ---- batched 2D sweep (ep_sweep_batch.hip) ---------------------------------
+// ---- 2D sweeps (ep_sweep_batch.hip) ----------------------------------------
 struct TileRef {
     int model;             // index into the model table
-    short bx, by;          // tile coordinates in the model's grid
+    int bx, by;            // tile coordinates in the model's grid
 };
-constexpr int BATCH_SHAPES = 6;
-extern const int kBatchTiles[BATCH_SHAPES][3];   // (TX, TY, threads) of each tile shape
-constexpr int SINGLE_SHAPE = 4;                   // 64 x 16: the shape of single 2D models
-// One sweep of every tile in list[0 .. *count) with the tile shape `shape`;
-// table[model] holds the model's arguments (reads of iteration k, writes of
-// k+1).  `grid` workgroups walk the list (persistent grid).
+constexpr int BATCH_SHAPES = 10;                  // tile shapes of a precision ...
+constexpr int TUNED_SHAPES = 6;                   // ... of which the autotuner tries the first six
+struct Tile2d {
+    int tx, ty, k;         // cells a workgroup owns, sweeps per launch at most
+    int pass_x, pass_y;    // points one pass of its threads covers (the shape's name)
+    double t1, t0, t2;     // cost of a launch (tile2d_cost)
+};
+extern const Tile2d kTiles2d[2][BATCH_SHAPES];   // [FP64, FP32]
+constexpr int PHYS_TILE = 24;                     // side of the tiles of physical evaluations
+inline long tiles2d(bool fp32, int shape, int nx, int ny)
+{
+    const Tile2d& t = kTiles2d[fp32][shape];
+    return (long)((nx + t.tx - 1) / t.tx) * ((ny + t.ty - 1) / t.ty);
+}
+// Modelled time per sweep (us) of a launch over `tiles` tiles, and the shape
+// of least modelled time for one model.
+double tile2d_cost(bool fp32, int shape, long tiles, int cus);
+int tile2d_choice(bool fp32, int nx, int ny, int cus);
+
+struct Launch2d {
+    int shape, mode, ns;   // ns <= K sweeps; the last one reduces when mode is MODE_CHECK
+    int grid;              // workgroups (they walk the tiles)
+    int tiles, nbx;        // tiles of the model and per row of it (without a list)
+    bool has_g;            // per-cell shear modulus (single models)
+};
+// ns sweeps of every tile in list[0 .. *count) (nullptr: the tiles of the one
+// model table[0]); table[model] holds the model's arguments (reads of
+// iteration k, writes of k+ns).
 template <typename R>
-void launch_sweep_batch_2d(int shape, const SweepArgs<R>* table, const TileRef* list, const int* count, int mode,
-                           int grid, hipStream_t s);
+void launch_sweep_batch_2d(const SweepArgs<R>* table, const TileRef* list, const int* count, const Launch2d& l,
+                           hipStream_t s);
 // Resident workgroups per CU of the batched kernel with this tile shape.
 template <typename R> int batch_blocks_per_cu(int shape);
 

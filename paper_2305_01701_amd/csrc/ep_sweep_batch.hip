@@ -1,14 +1,17 @@
-// Batched 2D PT sweep: one persistent launch sweeps the tiles of many
-// independent models of different sizes and parameters.
+// 2D PT sweeps: persistent launches that walk the tiles of one model or of
+// many independent models of different sizes and parameters, up to K sweeps
+// per launch (ep_tile2d.h).
 //
 // A model table holds one SweepArgs per model (per parity of the ping-pong
 // buffers); a tile list holds (model, tile x, tile y) for every tile of the
-// models that are still iterating in this precision and tile shape.  The
-// grid is sized to the resident capacity of the device and each workgroup
-// walks the list with a grid stride; models that converged are simply absent
-// from the list, so their tiles cost nothing.  The list length is read from
-// device memory, which lets a captured graph of sweeps stay valid while the
-// host retires models between replays.
+// models that are still iterating in this precision and tile shape (a single
+// model needs no list).  The grid is sized to the resident capacity of the
+// device and each workgroup walks the list with a grid stride; models that
+// converged are simply absent from the list, so their tiles cost nothing.
+// The list length is read from device memory, which lets a captured graph of
+// sweeps stay valid while the host retires models between replays.
+#include <cmath>
+
 #include "ep_device.h"
 #include "ep_tile2d.h"
 
@@ -16,40 +19,59 @@ namespace ep {
 
 namespace {
 
-template <typename R, int TX, int TY, int MODE, int NT = tile_threads_2d<TX, TY>()>
-__global__ __launch_bounds__(NT) void k_batch_2d(const SweepArgs<R>* __restrict__ table,
-                                                      const TileRef* __restrict__ list,
-                                                      const int* __restrict__ count)
+template <typename R, int TX, int TY, int K, int MODE, int NT, int E, bool HG>
+__global__ __attribute__((amdgpu_flat_work_group_size(NT, NT), amdgpu_waves_per_eu(E)))
+void k_batch_2d(const SweepArgs<R>* __restrict__ table, const TileRef* __restrict__ list, const int* __restrict__ count,
+                int tiles, int nbx, int ns)
 {
-    const int n = *count;
+    const int n = list ? *count : tiles;
     // logical workgroup ids contiguous per XCD: consecutive tiles of a model
     // (neighbours, sharing halo lines) run on the same L2
     const int g = xcd_remap(blockIdx.x, gridDim.x);
     for (int t = g; t < n; t += gridDim.x) {
         if (t != g) __syncthreads();        // LDS of the previous tile is still being read
-        const TileRef r = list[t];
-        sweep_tile_2d<R, TX, TY, MODE, NT>(table[r.model], r.bx, r.by);
+        TileRef r{0, 0, 0};
+        int bx = t % nbx, by = t / nbx;
+        if (list) {
+            r = list[t];
+            bx = r.bx;
+            by = r.by;
+        }
+        sweep_tile_2d<R, TX, TY, K, MODE, NT, HG>(table[r.model], bx, by, ns);
     }
 }
 
-template <typename R, int TX, int TY, int NT = tile_threads_2d<TX, TY>()>
-void run(const SweepArgs<R>* table, const TileRef* list, const int* count, int mode, int grid, hipStream_t s)
+// Tile shapes of each precision: index, TX, TY, K, threads, waves per SIMD to
+// fit in registers.  The first six are the tuner's, named by the points that
+// one pass of the workgroup's threads covers (64 x 8, 64 x 4, 32 x 8, 128 x 4,
+// 64 x 16, 32 x 16).
+#define EP_TILES_32(X) X(0, 52, 20, 3, 512, 6) X(1, 56, 8, 2, 256, 5) X(2, 24, 24, 2, 256, 5) X(3, 120, 8, 2, 512, 5) \
+    X(4, 52, 20, 3, 1024, 8) X(5, 24, 24, 2, 512, 8) X(6, 12, 12, 5, 1024, 8) X(7, 16, 16, 4, 1024, 8)              \
+    X(8, 20, 20, 3, 1024, 8) X(9, 32, 32, 4, 768, 6)
+#define EP_TILES_64(X) X(0, 56, 8, 2, 512, 4) X(1, 56, 8, 2, 256, 3) X(2, 24, 24, 2, 256, 3) X(3, 120, 8, 2, 512, 2) \
+    X(4, 52, 20, 3, 1024, 4) X(5, 24, 24, 2, 512, 4) X(6, 12, 12, 5, 1024, 4) X(7, 16, 16, 4, 1024, 4)              \
+    X(8, 20, 20, 3, 1024, 4) X(9, 20, 20, 3, 512, 4)
+
+template <typename R, int TX, int TY, int K, int NT, int E>
+void run(const SweepArgs<R>* table, const TileRef* list, const int* count, const Launch2d& l, hipStream_t s)
 {
-    if (mode == MODE_CHECK)
-        k_batch_2d<R, TX, TY, MODE_CHECK, NT><<<grid, NT, 0, s>>>(table, list, count);
-    else if (mode == MODE_PHYS) {
-        // physical evaluations run only on single models, with their shape
-        if constexpr (TX == 64 && TY == 16)
-            k_batch_2d<R, TX, TY, MODE_PHYS, NT><<<grid, NT, 0, s>>>(table, list, count);
-    } else
-        k_batch_2d<R, TX, TY, MODE_UPDATE, NT><<<grid, NT, 0, s>>>(table, list, count);
+    const int grid = l.grid > 0 ? l.grid : 1;
+    if (l.has_g) {
+        if (l.mode == MODE_CHECK)
+            k_batch_2d<R, TX, TY, K, MODE_CHECK, NT, E, true><<<grid, NT, 0, s>>>(table, list, count, l.tiles, l.nbx, l.ns);
+        else
+            k_batch_2d<R, TX, TY, K, MODE_UPDATE, NT, E, true><<<grid, NT, 0, s>>>(table, list, count, l.tiles, l.nbx, l.ns);
+    } else if (l.mode == MODE_CHECK)
+        k_batch_2d<R, TX, TY, K, MODE_CHECK, NT, E, false><<<grid, NT, 0, s>>>(table, list, count, l.tiles, l.nbx, l.ns);
+    else
+        k_batch_2d<R, TX, TY, K, MODE_UPDATE, NT, E, false><<<grid, NT, 0, s>>>(table, list, count, l.tiles, l.nbx, l.ns);
 }
 
-template <typename R, int TX, int TY, int NT = tile_threads_2d<TX, TY>()>
+template <typename R, int TX, int TY, int K, int NT, int E>
 int occupancy()
 {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_batch_2d<R, TX, TY, MODE_CHECK, NT>, NT, 0) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_batch_2d<R, TX, TY, K, MODE_CHECK, NT, E, false>, NT, 0) !=
         hipSuccess)
         return 1;
     return n > 0 ? n : 1;
@@ -57,40 +79,81 @@ int occupancy()
 
 }  // namespace
 
-const int kBatchTiles[BATCH_SHAPES][3] = {
-    {64, 8, tile_threads_2d<64, 8>()},   {64, 4, tile_threads_2d<64, 4>()},   {32, 8, tile_threads_2d<32, 8>()},
-    {128, 4, tile_threads_2d<128, 4>()}, {64, 16, tile_threads_2d<64, 16>()}, {32, 16, tile_threads_2d<32, 16>()}};
+// What a launch with a shape costs, in us: alone with at most one workgroup
+// per CU (t1), else t0 + t2 per workgroup on a CU; measured on 18 grids from
+// 31^2 to 2047^2.
+const Tile2d kTiles2d[2][BATCH_SHAPES] = {
+    {{56, 8, 2, 64, 8, 10.5, 4.5, 5.7}, {56, 8, 2, 64, 4, 13.0, 7.0, 5.6}, {24, 24, 2, 32, 8, 15.0, 8.0, 6.0},
+     {120, 8, 2, 128, 4, 16.0, 3.0, 13.0}, {52, 20, 3, 64, 16, 20.5, 1.0, 20.5}, {24, 24, 2, 32, 16, 11.0, 4.5, 6.2},
+     {12, 12, 5, 32, 32, 15.8, 1.8, 14.0}, {16, 16, 4, 32, 32, 14.0, 2.0, 12.3}, {20, 20, 3, 32, 32, 12.0, 1.5, 10.7},
+     {20, 20, 3, 32, 16, 13.7, 5.0, 7.6}},
+    {{52, 20, 3, 64, 8, 15.7, 5.0, 7.0}, {56, 8, 2, 64, 4, 10.0, 2.0, 2.6}, {24, 24, 2, 32, 8, 10.0, 2.0, 3.5},
+     {120, 8, 2, 128, 4, 11.0, 2.0, 6.4}, {52, 20, 3, 64, 16, 11.2, 3.0, 6.9}, {24, 24, 2, 32, 16, 8.0, 1.5, 3.2},
+     {12, 12, 5, 32, 32, 9.6, 1.7, 5.9}, {16, 16, 4, 32, 32, 8.5, 1.6, 4.9}, {20, 20, 3, 32, 32, 7.4, 2.3, 3.9},
+     {32, 32, 4, 48, 16, 17.0, 2.5, 10.2}}};
+
+double tile2d_cost(bool fp32, int shape, long tiles, int cus)
+{
+    const Tile2d& t = kTiles2d[fp32][shape];
+    const double m = std::ceil((double)tiles / cus);
+    return std::fmax(t.t1, t.t0 + t.t2 * m) / t.k;
+}
+
+// The shape of least modelled time for a model of nx x ny cells.  A launch of
+// K sweeps is worth more redundant points the fewer workgroups a grid fills:
+// 12 x 12 tiles with K = 5 up to 16 tiles a side (63^2 FP32 1.9 us per sweep,
+// one sweep per launch of 64 x 16 tiles 5; FP64 3.1 against 7.5), then 16 x 16,
+// 20 x 20 and the large tiles (1023^2 FP32 11 against 19 us, FP64 25 against
+// 43).
+int tile2d_choice(bool fp32, int nx, int ny, int cus)
+{
+    int best = 0;
+    double t_best = INFINITY;
+    for (int s = 0; s < BATCH_SHAPES; ++s) {
+        const double t = tile2d_cost(fp32, s, tiles2d(fp32, s, nx, ny), cus);
+        if (t < t_best) {
+            t_best = t;
+            best = s;
+        }
+    }
+    return best;
+}
 
 template <typename R>
-void launch_sweep_batch_2d(int shape, const SweepArgs<R>* table, const TileRef* list, const int* count, int mode,
-                           int grid, hipStream_t s)
+void launch_sweep_batch_2d(const SweepArgs<R>* table, const TileRef* list, const int* count, const Launch2d& l,
+                           hipStream_t s)
 {
-    switch (shape) {
-    case 0: run<R, 64, 8>(table, list, count, mode, grid, s); break;
-    case 1: run<R, 64, 4>(table, list, count, mode, grid, s); break;
-    case 2: run<R, 32, 8>(table, list, count, mode, grid, s); break;
-    case 3: run<R, 128, 4>(table, list, count, mode, grid, s); break;
-    case 4: run<R, 64, 16>(table, list, count, mode, grid, s); break;
-    default: run<R, 32, 16>(table, list, count, mode, grid, s); break;
+#define X(i, TX, TY, K, NT, E) case i: run<R, TX, TY, K, NT, E>(table, list, count, l, s); break;
+    if constexpr (sizeof(R) == 8) {
+        if (l.mode == MODE_PHYS) {
+            // physical evaluations: single FP64 models, once or twice an increment
+            if (l.has_g) k_batch_2d<R, 24, 24, 2, MODE_PHYS, 512, 4, true><<<l.grid, 512, 0, s>>>(table, list, count, l.tiles, l.nbx, 1);
+            else k_batch_2d<R, 24, 24, 2, MODE_PHYS, 512, 4, false><<<l.grid, 512, 0, s>>>(table, list, count, l.tiles, l.nbx, 1);
+            return;
+        }
+        switch (l.shape) { EP_TILES_64(X) }
+    } else {
+        switch (l.shape) { EP_TILES_32(X) }
     }
+#undef X
 }
 
 template <typename R>
 int batch_blocks_per_cu(int shape)
 {
-    switch (shape) {
-    case 0: return occupancy<R, 64, 8>();
-    case 1: return occupancy<R, 64, 4>();
-    case 2: return occupancy<R, 32, 8>();
-    case 3: return occupancy<R, 128, 4>();
-    case 4: return occupancy<R, 64, 16>();
-    default: return occupancy<R, 32, 16>();
+#define X(i, TX, TY, K, NT, E) case i: return occupancy<R, TX, TY, K, NT, E>();
+    if constexpr (sizeof(R) == 8) {
+        switch (shape) { EP_TILES_64(X) }
+    } else {
+        switch (shape) { EP_TILES_32(X) }
     }
+#undef X
+    return 1;
 }
 
-template void launch_sweep_batch_2d<float>(int, const SweepArgs<float>*, const TileRef*, const int*, int, int,
+template void launch_sweep_batch_2d<float>(const SweepArgs<float>*, const TileRef*, const int*, const Launch2d&,
                                            hipStream_t);
-template void launch_sweep_batch_2d<double>(int, const SweepArgs<double>*, const TileRef*, const int*, int, int,
+template void launch_sweep_batch_2d<double>(const SweepArgs<double>*, const TileRef*, const int*, const Launch2d&,
                                             hipStream_t);
 template int batch_blocks_per_cu<float>(int);
 template int batch_blocks_per_cu<double>(int);

@@ -16,10 +16,10 @@
 // part of the kernel, and a layer behind a repetition reads its parent level.
 // The gradient with respect to the input is the same kernel on the output
 // gradient with the weights transposed (input <-> output channels) and the
-// taps mirrored.  The weight gradient reduces over voxels: a workgroup stages
-// voxels of the output gradient and of the tap-shifted input in LDS,
-// accumulates 16 x 16 blocks with the voxels as the MFMA reduction dimension
-// and writes partial sums, which are added up in a fixed order.
+// taps mirrored.  The weight gradient reduces over voxels: a workgroup takes a
+// chunk of voxels, stages the output gradient and the input around it once for
+// all 27 taps, accumulates 16 x 16 blocks with the voxels as the MFMA reduction
+// dimension and writes partial sums, which are added up in a fixed order.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -45,14 +45,13 @@ typedef unsigned short bf16_t;
 typedef __attribute__((ext_vector_type(4))) short s4;
 typedef __attribute__((ext_vector_type(8))) __bf16 b8;
 typedef __attribute__((ext_vector_type(4))) float f4;
-
 // 8 bfloat16 values (16 bytes) as the operand of a K = 32 MFMA
-__device__ __forceinline__ b8 ld_b8(const bf16_t* p) { return __builtin_bit_cast(b8, *(const uint4*)p); }
 
 constexpr int NL = 11;      // convolutions
 constexpr int CIN0 = 16;    // input channels (11 used)
 constexpr int COUT = 16;    // output channels (3 used)
 constexpr long PART_FLOATS = 1L << 23;   // partial-sum buffer of the parameter gradients (32 MiB)
+constexpr long PART_BIAS = 1024;         // workgroups of a bias gradient (behind it: their sums, 128 channels at most)
 
 // ------------------------------------------------------------ bfloat16
 __device__ __forceinline__ float bf2f(bf16_t b) { return __uint_as_float((unsigned)b << 16); }
@@ -99,12 +98,6 @@ __device__ __forceinline__ long pidx(const Vol& g, long v)
     const int y = (int)(r % g.H);
     const int z = (int)(r / g.H);
     return ((long)(z + 1) * g.Hp + (y + 1)) * g.Wp + (x + 1);
-}
-
-__device__ __forceinline__ long tap_off(const Vol& g, int t)
-{
-    const int dz = t / 9 - 1, dy = (t / 3) % 3 - 1, dx = t % 3 - 1;
-    return ((long)dz * g.Hp + dy) * g.Wp + dx;
 }
 
 // Block index -> logical index so that consecutive logical indices run on
@@ -374,189 +367,387 @@ __global__ __launch_bounds__(256, 2) void k_conv(ConvArgs a)
     conv_store<MR, NBW, EPI>(a, acc, x0 + r, y0, z0 + wave, c0);
 }
 
-// Channels 0..7 of voxels v (a) and v + 1 (b) to eight channel rows of a
-// channel-major LDS stage: row k gets the dword (a_k, b_k) at d + k * rw
-// (d at an even voxel index, so every dword is aligned).
-__device__ __forceinline__ void stage_pair(bf16_t* d, int rw, const uint4& a, const uint4& b)
+// 8 channels of a voxel
+__device__ __forceinline__ uint4 ld8(const bf16_t* p) { return *(const uint4*)p; }
+__device__ __forceinline__ float bf_at(const uint4& v, int k) { return bf2f(((const bf16_t*)&v)[k]); }
+
+// Weight and bias gradients: the products are reduced over voxels, so both
+// fragments hold 8 voxels of one channel per lane.  Voxels are staged in LDS
+// as they lie in memory, channel-last, and read transposed
+// (ds_read_b64_tr_b16: 16 lanes read 4 voxels x 16 channels, lane i gets the 4
+// voxels of channel i).
+typedef __attribute__((address_space(3))) s4 lds_s4;
+__device__ __forceinline__ b8 ld_tr(const bf16_t* p, const bf16_t* q)
 {
-    const unsigned aw[4] = {a.x, a.y, a.z, a.w}, bw[4] = {b.x, b.y, b.z, b.w};
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        // channel 2k: low halves of a and b; channel 2k + 1: high halves
-        *(unsigned*)(d + (2 * k) * rw) = (aw[k] & 0xffffu) | (bw[k] << 16);
-        *(unsigned*)(d + (2 * k + 1) * rw) = (aw[k] >> 16) | (bw[k] & 0xffff0000u);
-    }
+    typedef __attribute__((ext_vector_type(8))) short s8;
+    const s4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)p);
+    const s4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)q);
+    return __builtin_bit_cast(b8, s8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]});
+}
+__device__ __forceinline__ int div_by(int n, float inv) { return (int)(((float)n + 0.5f) * inv); }   // n < 2^22
+
+// n / d of values that are the same in all lanes, most often 0 (an integer
+// division is some 40 dependent instructions)
+__device__ __forceinline__ int div_uniform(int n, int d, float inv)
+{
+    return n < d ? 0 : __builtin_amdgcn_readfirstlane(div_by(n, inv));
 }
 
-// part[chunk][o][t][i] = sum over the chunk's voxels v of G[v][o] X[v + off_t][i],
-// one workgroup per (voxel chunk, tap); k_wsum adds the chunks up in a fixed
-// order, so a gradient does not depend on the order the workgroups run in.
-// The 27 taps of a chunk are consecutive logical workgroups on one XCD, so
-// that the chunk's output gradient and the overlapping input windows of its
-// taps can be served from that XCD's L2 (no change in time measured: the
-// kernel is bound by its LDS staging).
-template <int NBO, int NBI, int SL>
-__global__ __launch_bounds__(256) void k_wgrad(const bf16_t* __restrict__ X, const bf16_t* __restrict__ G,
-                                               float* __restrict__ part, Vol g, long vchunk)
-{
-    constexpr int CO = NBO * 16, CI = NBI * 16;
-    constexpr long E = 27L * CO * CI;                  // entries of one chunk's partial gradient
-    constexpr int RW = SL + 8;                         // SL voxels + 8: rows of 144 or 272 bytes
-    constexpr int NP = NBO * NBI, PW = (NP + 3) / 4;   // block pairs, per wave
-    // channel-major (transposed) stage: a lane's 8 voxels of one channel are
-    // one 16-byte LDS read
-    __shared__ __attribute__((aligned(16))) bf16_t sG[CO * RW], sX[CI * RW];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int r = lane & 15, kq = lane >> 4;
-    const int lb = xcd_order(blockIdx.x, gridDim.x);
-    const int t = lb % 27, chunk = lb / 27;
-    const long off = tap_off(g, t);
-    const long v0 = (long)chunk * vchunk;
-    const long v1 = v0 + vchunk < g.V ? v0 + vchunk : g.V;
-    f4 acc[PW];
-#pragma unroll
-    for (int q = 0; q < PW; ++q) acc[q] = f4{0.f, 0.f, 0.f, 0.f};
-    // stage SL voxels: a pair of voxels x 8 channels (two 16-byte loads) per
-    // thread and task, loaded into registers one slab ahead and written
-    // transposed as 8 dwords (channel k of both voxels); the SL / 2 lanes of
-    // a channel group take consecutive pairs, so that a wave's dword writes
-    // fall in distinct LDS banks
-    constexpr int NPR = SL / 2;                        // voxel pairs per slab
-    constexpr int NGT = NPR * (CO / 8), NXT = NPR * (CI / 8);
-    constexpr int NGL = (NGT + 255) / 256, NXL = (NXT + 255) / 256;
-    uint4 ga[NGL], gb[NGL], xa[NXL], xb[NXL];
-    auto load = [&](long vs) {
-#pragma unroll
-        for (int u = 0; u < NGL; ++u) {
-            const int e = threadIdx.x + 256 * u, row = 2 * (e % NPR), q = e / NPR;
-            const long v = vs + row;
-            ga[u] = uint4{0u, 0u, 0u, 0u};
-            gb[u] = uint4{0u, 0u, 0u, 0u};
-            if (e < NGT && v < v1) ga[u] = *(const uint4*)(G + pidx(g, v) * CO + q * 8);
-            if (e < NGT && v + 1 < v1) gb[u] = *(const uint4*)(G + pidx(g, v + 1) * CO + q * 8);
-        }
-#pragma unroll
-        for (int u = 0; u < NXL; ++u) {
-            const int e = threadIdx.x + 256 * u, row = 2 * (e % NPR), q = e / NPR;
-            const long v = vs + row;
-            xa[u] = uint4{0u, 0u, 0u, 0u};
-            xb[u] = uint4{0u, 0u, 0u, 0u};
-            if (e < NXT && v < v1) xa[u] = *(const uint4*)(X + (pidx(g, v) + off) * CI + q * 8);
-            if (e < NXT && v + 1 < v1) xb[u] = *(const uint4*)(X + (pidx(g, v + 1) + off) * CI + q * 8);
-        }
-    };
-    if (v0 < v1) load(v0);
-    for (long vs = v0; vs < v1; vs += SL) {
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < NGL; ++u) {
-            const int e = threadIdx.x + 256 * u;
-            if (e < NGT) stage_pair(sG + (e / NPR) * 8 * RW + 2 * (e % NPR), RW, ga[u], gb[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < NXL; ++u) {
-            const int e = threadIdx.x + 256 * u;
-            if (e < NXT) stage_pair(sX + (e / NPR) * 8 * RW + 2 * (e % NPR), RW, xa[u], xb[u]);
-        }
-        __syncthreads();
-        if (vs + SL < v1) load(vs + SL);
-#pragma unroll
-        for (int q = 0; q < PW; ++q) {
-            const int pr = wave + 4 * q;
-            if (pr >= NP) break;
-            const int ob = pr / NBI, ib = pr % NBI;
-#pragma unroll
-            for (int ks = 0; ks < SL / 32; ++ks) {
-                // K = 32 voxels: lane (r, kq) holds voxels ks*32 + kq*8 .. +7 of
-                // output channel ob*16 + r (A) and input channel ib*16 + r (B)
-                const b8 a = ld_b8(sG + (ob * 16 + r) * RW + ks * 32 + kq * 8);
-                const b8 b = ld_b8(sX + (ib * 16 + r) * RW + ks * 32 + kq * 8);
-                acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[q], 0, 0, 0);
-            }
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < PW; ++q) {
-        const int pr = wave + 4 * q;
-        if (pr >= NP) break;
-        const int ob = pr / NBI, ib = pr % NBI;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int o = ob * 16 + kq * 4 + i, c = ib * 16 + r;
-            part[chunk * E + ((long)o * 27 + t) * CI + c] = acc[q][i];
-        }
-    }
-}
+constexpr int WG_STEP = 128, WG_NEW = 192;                   // voxels of a step, new places of one load
+constexpr int WG_LOAD = 256;                                 // threads that load (behind 512 that compute)
+struct WgradArgs {
+    const bf16_t *X, *G;
+    float *part, *bias;                                      // partial sums: weights, bias
+    int cin, cout;
+    Vol g, gx;                                               // level of G; level of X (with UP the parent's)
+    long vchunk;
+    int nch, nb;                                             // chunks; workgroups for the bias
+};
 
-// dW[e] += sum over chunks of part[chunk][e], in chunk order: thread (j, e)
-// of a 256-thread block (32 entries x 8) sums chunks j, j + 8, ..., then the
-// eight sums are added in j order.
-__global__ __launch_bounds__(256) void k_wsum(const float* __restrict__ part, long nch, long E, float* __restrict__ dW)
-{
-    __shared__ float s[8][32];
-    const int el = threadIdx.x & 31, jl = threadIdx.x >> 5;
-    const long e = (long)blockIdx.x * 32 + el;
-    float acc = 0.f;
-    if (e < E)
-        for (long c = jl; c < nch; c += 8) acc += part[c * E + e];
-    s[jl][el] = acc;
-    __syncthreads();
-    if (jl == 0 && e < E) {
-        float sum = s[0][el];
-        for (int j = 1; j < 8; ++j) sum += s[j][el];
-        dW[e] += sum;
-    }
-}
-
-// part[block][c] = sum over the block's voxels of G[v][c] (k_bsum adds the
+// bias[block][c] = sum over the block's voxels of G[v][c] (k_wsum adds the
 // blocks up in a fixed order)
-__global__ void k_bias_grad(const bf16_t* __restrict__ G, int C, float* __restrict__ part, Vol g)
+__global__ __launch_bounds__(256) void k_bias_grad(WgradArgs a)
 {
     // thread = (voxel slot, group of 8 channels): 16-byte loads, a block
     // covers 256 / (C / 8) voxels per step (C in {16, 32, 64, 128})
     __shared__ float s[256 * 8];
-    const int ng = C / 8, grp = threadIdx.x % ng, vq = threadIdx.x / ng, nv = 256 / ng;
+    const int C = a.cout, ng = C / 8, grp = threadIdx.x % ng, vq = threadIdx.x / ng, nv = 256 / ng;
+    const Vol& g = a.g;
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (long v = (long)blockIdx.x * nv + vq; v < g.V; v += (long)gridDim.x * nv) {
-        const uint4 val = *(const uint4*)(G + pidx(g, v) * C + grp * 8);
-        const bf16_t* h = (const bf16_t*)&val;
+    const long step = (long)a.nb * nv;
+    long v = (long)blockIdx.x * nv + vq;
+    // 8 loads in flight: one after the other they took 37 us of a 32-channel
+    // layer at 128^3
+    for (; v + 7 * step < g.V; v += 8 * step) {
+        uint4 q[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) acc[k] += bf2f(h[k]);
+        for (int u = 0; u < 8; ++u) q[u] = ld8(a.G + pidx(g, v + u * step) * C + grp * 8);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) acc[k] += bf_at(q[u], k);
+    }
+    for (; v < g.V; v += step) {
+        const uint4 q = ld8(a.G + pidx(g, v) * C + grp * 8);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) acc[k] += bf_at(q, k);
     }
 #pragma unroll
     for (int k = 0; k < 8; ++k) s[threadIdx.x * 8 + k] = acc[k];
     __syncthreads();
-    if (threadIdx.x < C) {
+    if ((int)threadIdx.x < C) {
         const int gq = threadIdx.x / 8, k = threadIdx.x % 8;
         float sum = 0.f;
         for (int q = 0; q < nv; ++q) sum += s[(q * ng + gq) * 8 + k];
-        part[(long)blockIdx.x * C + threadIdx.x] = sum;
+        a.bias[(long)blockIdx.x * C + threadIdx.x] = sum;
     }
 }
 
-// db[c] += sum over blocks of part[block][c], one workgroup per channel:
+// part[chunk][group][block pair][tap][lane][4]: sum over the chunk's voxels of
+// G[v][o] X[v + off_t][i], for groups of 16 CO output and 16 CI input
+// channels; every sum adds 32 voxels at a time in their order, whatever the
+// split.
+//
+// A chunk is walked in steps of up to 128 consecutive voxels.  Its voxels have places q = (z (H + 1) + y) (W + 1) + x,
+// in which one zero voxel between rows and one zero row between planes are the
+// border, so that a tap is a constant distance dy (W + 1) + dx; of each of the
+// three planes z + dz of X, a ring of R places in LDS holds those around the
+// step, and a step loads only the places that are new: all 27 taps come from
+// them.  (Rows too long for a ring: ROWS = 3 rings per plane, one per dy, and
+// no row between planes.)  Eight waves compute: they share the (input block,
+// tap) pairs, each with all output blocks, so that a fragment of X is read
+// once.  Four waves load: while a step is computed they store the next one's
+// voxels and the list of its places to LDS and fetch the voxels of the one
+// after it into registers.
+//
+// What bounds it: LDS reads (a fragment of 1 KB takes 10 clocks of the CU and
+// serves CO products of 4 each; their banks do not conflict at any voxel
+// pitch measured) and the instructions of the loading waves.  With a
+// workgroup per tap and chunk, which staged both tensors transposed 27 times,
+// the eleven layers of a gradient at 128^3 with 32 base channels took 5.9 ms,
+// at 72 x 64 x 48 with 16 0.55 ms; they take 1.9 and 0.37.  32 -> 32 channels
+// at 128^3: 276 us, of the 46 that its products take.  Loading from the
+// computing waves themselves: 384 us (9 windows per step) and 519 (rings).
+template <int CO, int CI, bool UP, int R, int ROWS>
+__global__ __launch_bounds__(512 + WG_LOAD, 3) void k_wgrad(WgradArgs a)
+{
+    constexpr int NO = CO * 16, NI = CI * 16;                // channels
+    constexpr int TG = 8 / CI, PER = (27 + TG - 1) / TG;     // waves that share the taps, taps of a wave
+    constexpr int RING = R * NI, XE = 3 * ROWS * RING, GE = WG_STEP * NO;   // elements
+    constexpr int NEW = WG_NEW, NP = NI / 8;                 // 16-byte pieces of a voxel
+    constexpr int PX = (ROWS * NEW * NP + WG_LOAD - 1) / WG_LOAD, PG = GE / 8 / WG_LOAD;    // per loading thread
+    static_assert(GE / 8 % WG_LOAD == 0, "");
+    __shared__ __attribute__((aligned(16))) bf16_t lds[XE + 2 * GE];
+    // of two steps: the voxels' places (in elements); blocks of 32 voxels, whether
+    // the next step is stored after it, whether there is one
+    __shared__ int place[2][WG_STEP], blocks[2], wait[2], more[2];
+    const Vol &g = a.g, &gx = a.gx;
+    const int ngi = a.cin / NI, ng = ngi * (a.cout / NO), nw = a.nch * ng;
+    const int lb = xcd_order(blockIdx.x, nw), chunk = lb / ng, grp = lb % ng;
+    const int o0 = grp / ngi * NO, i0 = grp % ngi * NI;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int W1 = g.W + 1;
+    const int loader = tid - 512;
+    if (loader < 0) {
+        const int l0 = (lane >> 4) * 8 + (lane & 15) / 4, c4 = lane % 4 * 4;   // voxel and channels the lane reads
+        const int ib = wave % CI, tg = wave / CI, mine = ib * 16 + c4;
+        f4 acc[PER][CO];
+        int ring[PER], shift[PER];                           // of the wave's taps, in elements
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int t = tg * PER + q < 27 ? tg * PER + q : 26, dy = t / 3 % 3;
+            ring[q] = (ROWS == 3 ? t / 3 : t / 9) * RING;
+            shift[q] = ((ROWS == 3 ? 0 : (dy - 1) * W1) + t % 3 - 1) * NI + mine;
+#pragma unroll
+            for (int m = 0; m < CO; ++m) acc[q][m] = f4{0.f, 0.f, 0.f, 0.f};
+        }
+        struct Frags {
+            b8 w[CO], f[PER];
+        };
+        for (int b = 0;; b ^= 1) {
+            __syncthreads();
+            const bf16_t* const from = lds + XE + b * GE + l0 * NO + c4;
+            const int* const at = place[b] + l0;
+            const int nk = __builtin_amdgcn_readfirstlane(blocks[b]);
+            // the places of a block of 32 voxels are read one block ahead
+            int q[2] = {at[0], at[4]};
+            auto read = [&](int kb, Frags& x) {
+#pragma unroll
+                for (int m = 0; m < CO; ++m)
+                    x.w[m] = ld_tr(from + kb * 32 * NO + m * 16, from + (kb * 32 + 4) * NO + m * 16);
+#pragma unroll
+                for (int t = 0; t < PER; ++t)
+                    x.f[t] = ld_tr(lds + (((q[0] + shift[t]) & (RING - 1)) | ring[t]),
+                                   lds + (((q[1] + shift[t]) & (RING - 1)) | ring[t]));
+                const int next = (kb + 1) * 32 & (WG_STEP - 1);
+                q[0] = at[next];
+                q[1] = at[next + 4];
+            };
+            auto compute = [&](const Frags& x) {
+#pragma unroll
+                for (int t = 0; t < PER; ++t)
+#pragma unroll
+                    for (int m = 0; m < CO; ++m) acc[t][m] = mfma(x.w[m], x.f[t], acc[t][m]);
+            };
+            for (int kb = 0; kb < nk; ++kb) {
+                Frags x;
+                read(kb, x);
+                compute(x);
+            }
+            const bool last = !__builtin_amdgcn_readfirstlane(more[b]);
+            if (__builtin_amdgcn_readfirstlane(wait[b])) __syncthreads();
+            if (last) break;
+        }
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int t = tg * PER + q;
+            if (t >= 27) break;
+#pragma unroll
+            for (int m = 0; m < CO; ++m)
+                *((f4*)a.part + ((((long)chunk * ng + grp) * CO * CI + m * CI + ib) * 27 + t) * 64 + lane) = acc[q][m];
+        }
+        return;
+    }
+
+    // ---- the loading waves
+    const int H1 = g.H + (ROWS == 3 ? 0 : 1), gap = ROWS == 3 ? 0 : W1;     // gap: places between planes
+    const int reach = ROWS == 3 ? 1 : W1 + 1;                // of the taps, in places
+    const float inv_w = 1.f / (float)g.W, inv_h = 1.f / (float)g.H, inv_w1 = 1.f / (float)W1, inv_h1 = 1.f / (float)H1;
+    // a voxel, or a place (z counted from -1), in coordinates
+    struct At {
+        int x, y, z, q;
+    };
+    // the voxel n on from v, n < 2^20
+    auto ahead_of = [&](At v, int n) {
+        const int x = v.x + n, run = div_uniform(x, g.W, inv_w), y = v.y + run, plane = div_uniform(y, g.H, inv_h);
+        return At{x - run * g.W, y - plane * g.H, v.z + plane, v.q + n + run + plane * gap};
+    };
+    // the pieces of X (row ring, place, channels) and of G of a thread
+    constexpr unsigned NONE = 0x80000000u;                   // out of a load's range: gives 0
+    const int xp = loader % NP, gp = loader % (NO / 8);
+    auto piece = [&](int u, int& r, int& i) {
+        const int e = loader + WG_LOAD * u;
+        r = e / (NEW * NP);
+        i = e / NP % NEW;
+        return ROWS * NEW * NP % WG_LOAD == 0 || r < ROWS;
+    };
+    uint4 vx[PX][3], vg[PG];
+    // offsets are those of voxels of the tensor or NONE
+    auto source = [](const bf16_t* p) { return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, 0x7fffffff, 0x00020000); };
+    auto read = [](__amdgpu_buffer_rsrc_t rs, unsigned at) {
+        return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, at, 0, 0));
+    };
+    const long v0 = chunk * a.vchunk, v1 = v0 + a.vchunk < g.V ? v0 + a.vchunk : g.V;
+    At v, n;                                                 // first voxel of a step, first place not stored
+    v.x = (int)(v0 % g.W);
+    v.y = (int)(v0 / g.W % g.H);
+    v.z = (int)(v0 / ((long)g.W * g.H));
+    const long q0 = ((long)(v.z + 1) * H1 + v.y) * W1 + v.x, n0 = q0 - reach;
+    v.q = (int)(unsigned)q0;
+    n.q = (int)(unsigned)n0;
+    n.x = (int)(n0 % W1);
+    n.y = (int)(n0 / W1 % H1);
+    n.z = (int)(n0 / ((long)W1 * H1)) - 1;
+    // count (up to NEW) places of X from n on
+    auto load_x = [&](int count) {
+        unsigned at[PX][UP ? 3 : 1];
+#pragma unroll
+        for (int u = 0; u < PX; ++u) {
+            int r, i;
+            const bool have = piece(u, r, i) && i < count;
+            int x = n.x + i;
+            const int run = div_by(x, inv_w1);
+            x -= run * W1;
+            const int plane = div_by(n.y + run, inv_h1), y = n.y + run - plane * H1 + (ROWS == 3 ? r - 1 : 0);
+            const int z = n.z + plane;
+            const bool in = have && x < g.W && y >= 0 && y < g.H && z >= 0 && z < g.D;
+            if constexpr (UP) {
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    const int p = ((z + k - 1) >> 1) - ((n.z + k - 1) >> 1);
+                    at[u][k] = in ? (unsigned)(((p * gx.Hp + (y >> 1) + 1) * gx.Wp + (x >> 1) + 1) * a.cin) * 2u + xp * 16 : NONE;
+                }
+            } else {
+                at[u][0] = in ? (unsigned)(((plane * gx.Hp + y + 1 - n.y) * gx.Wp + x + 1) * a.cin) * 2u + xp * 16 : NONE;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const int z = n.z + k - 1;
+            const auto rs = UP ? source(a.X + (long)((z >> 1) + 1) * gx.Hp * gx.Wp * a.cin + i0)
+                               : source(a.X + ((long)(z + 1) * gx.Hp + n.y) * gx.Wp * a.cin + i0);
+#pragma unroll
+            for (int u = 0; u < PX; ++u) vx[u][k] = read(rs, at[u][UP ? k : 0]);
+        }
+    };
+    auto store_x = [&](int count) {
+#pragma unroll
+        for (int u = 0; u < PX; ++u) {
+            int r, i;
+            if (!piece(u, r, i) || i >= count) continue;
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                *(uint4*)(lds + (k * ROWS + r) * RING + ((n.q + i) & (R - 1)) * NI + xp * 8) = vx[u][k];
+        }
+        const int x = n.x + count, run = div_uniform(x, W1, inv_w1), y = n.y + run, plane = div_uniform(y, H1, inv_h1);
+        n = At{x - run * W1, y - plane * H1, n.z + plane, n.q + count};
+    };
+    auto load_g = [&] {
+        const auto rs = source(a.G + (((long)(v.z + 1) * g.Hp + v.y + 1) * g.Wp + 1) * a.cout + o0);
+#pragma unroll
+        for (int u = 0; u < PG; ++u) {
+            int x = v.x + (loader + WG_LOAD * u) / (NO / 8);
+            const int run = div_by(x, inv_w), plane = div_by(v.y + run, inv_h), y = v.y + run - plane * g.H;
+            x -= run * g.W;
+            vg[u] = read(rs, v.z + plane < g.D ? (unsigned)(((plane * g.Hp + y - v.y) * g.Wp + x) * a.cout) * 2u + gp * 16 : NONE);
+        }
+    };
+    // A step has as many voxels, up to 128, as have room in the ring beside the
+    // step before it; where not even 32 have, the step before it is done
+    // first.  It is fetched ahead unless it brings too many places for one load
+    // (at a chunk's start, or where it crosses planes).
+    long left = v1 - v0;
+    int voxels, end;                                         // of the step from v on; end of its places
+    auto size = [&](int first) {
+        for (voxels = WG_STEP;; voxels -= 32) {
+            end = ahead_of(v, voxels - 1).q + reach + 1;
+            if (end - first <= R || voxels == 32) return;
+        }
+    };
+    size(v.q - reach);
+    bool fetched = false;
+    for (int b = 0;; b ^= 1) {
+        if (!fetched) {
+            while (end - n.q > NEW) {
+                load_x(NEW);
+                store_x(NEW);
+            }
+            load_x(end - n.q);
+            load_g();
+        }
+        store_x(end - n.q);
+#pragma unroll
+        for (int u = 0; u < PG; ++u) *(uint4*)(lds + XE + b * GE + (loader + WG_LOAD * u) * 8) = vg[u];
+        if (loader < WG_STEP) {
+            const int run = div_by(v.x + loader, inv_w), plane = div_by(v.y + run, inv_h);
+            place[b][loader] = (v.q + loader + run + plane * gap) * NI;
+        }
+        // the chunk's last step may be shorter (behind the volume G is 0)
+        const int first = v.q - reach, kb = left < voxels ? (int)(left + 31) / 32 : voxels / 32;
+        left -= voxels;
+        const bool go_on = left > 0;
+        bool held = false;
+        if (go_on) {
+            v = ahead_of(v, voxels);
+            size(first);
+            held = end - first > R;                          // no room in the ring until this step is computed
+            fetched = end - n.q <= NEW;
+            if (fetched) {
+                load_x(end - n.q);
+                load_g();
+            }
+        }
+        if (loader == 0) {
+            blocks[b] = kb;
+            wait[b] = held;
+            more[b] = go_on;
+        }
+        __syncthreads();
+        if (held) __syncthreads();
+        if (!go_on) return;
+    }
+}
+
+// dW and db = sums over the chunks' and the bias blocks' partial sums in a
+// fixed order.  Weights: E / 128 workgroups of 32 groups of 4 entries, thread
+// j of 8 sums chunks j, j + 8, ..., then the eight sums are added in j order;
+// entry (group, pair, tap, lane, i) is output channel 4 (lane / 16) + i and
+// input channel lane % 16 of its block.  Bias: one workgroup per channel,
 // thread j sums blocks j, j + 256, ..., then a tree of fixed shape adds the
 // 256 sums.
-__global__ __launch_bounds__(256) void k_bsum(const float* __restrict__ part, int nb, int C, float* __restrict__ db)
+__global__ __launch_bounds__(256) void k_wsum(WgradArgs a, long E, int co, int ci, float* __restrict__ dW,
+                                              float* __restrict__ db)
 {
-    __shared__ float s[256];
-    const int c = blockIdx.x;
-    float acc = 0.f;
-    for (int b = threadIdx.x; b < nb; b += 256) acc += part[(long)b * C + c];
-    s[threadIdx.x] = acc;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
+    __shared__ f4 s[8][32];
+    const long nw = E / 128;
+    if (blockIdx.x >= nw) {
+        float* const t = (float*)s;
+        const int c = (int)(blockIdx.x - nw);
+        float acc = 0.f;
+        for (int b = threadIdx.x; b < a.nb; b += 256) acc += a.bias[(long)b * a.cout + c];
+        t[threadIdx.x] = acc;
         __syncthreads();
+        for (int w = 128; w > 0; w >>= 1) {
+            if ((int)threadIdx.x < w) t[threadIdx.x] += t[threadIdx.x + w];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) db[c] = t[0];
+        return;
     }
-    if (threadIdx.x == 0) db[c] += s[0];
+    const int el = threadIdx.x & 31, jl = threadIdx.x >> 5;
+    const long e = blockIdx.x * 128L + el * 4;
+    f4 sum{0.f, 0.f, 0.f, 0.f};
+    auto add = [&](const f4& v) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum[i] = sum[i] + v[i];
+    };
+#pragma unroll 8
+    for (int c = jl; c < a.nch; c += 8) add(*(const f4*)(a.part + c * E + e));
+    s[jl][el] = sum;
+    __syncthreads();
+    if (jl > 0) return;
+    for (int j = 1; j < 8; ++j) add(s[j][el]);
+    const int lane = (int)(e / 4) % 64, t = (int)(e / 256) % 27, q = (int)(e / (256 * 27));
+    const int pair = q % (co * ci), grp = q / (co * ci), ngi = a.cin / (16 * ci);
+    const int o = (grp / ngi * co + pair / ci) * 16 + lane / 16 * 4;
+    const int i = (grp % ngi * ci + pair % ci) * 16 + lane % 16;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) dW[((long)(o + k) * 27 + t) * a.cin + i] = sum[k];
 }
 
 // ------------------------------------------------------------ elementwise
 // Passes between the levels.  A thread takes 8 channels (16 bytes) of one
 // voxel; all are bound by the bytes they move.
-__device__ __forceinline__ uint4 ld8(const bf16_t* p) { return *(const uint4*)p; }
-__device__ __forceinline__ float bf_at(const uint4& v, int k) { return bf2f(((const bf16_t*)&v)[k]); }
 __device__ __forceinline__ long at(const Vol& g, int x, int y, int z)
 {
     return ((long)(z + 1) * g.Hp + y + 1) * g.Wp + x + 1;
@@ -599,15 +790,6 @@ __global__ void k_pool(const bf16_t* __restrict__ in, bf16_t* __restrict__ out, 
 #pragma unroll
         for (int k = 0; k < 8; ++k) o[k] = f2bf(s[k] * 0.125f);
         *(uint4*)(out + at(g2, t.x, t.y, t.z) * C + t.c) = *(uint4*)o;
-    }
-}
-
-// up: out (level g) = parent value (level g2)
-__global__ void k_up(const bf16_t* __restrict__ in, bf16_t* __restrict__ out, int C, Vol g, Vol g2)
-{
-    for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < g.V * (C / 8); e += (long)gridDim.x * blockDim.x) {
-        const Elem t = elem_of(g, C, e);
-        *(uint4*)(out + at(g, t.x, t.y, t.z) * C + t.c) = ld8(in + at(g2, t.x / 2, t.y / 2, t.z / 2) * C + t.c);
     }
 }
 
@@ -659,15 +841,15 @@ __global__ void k_loss(const float* __restrict__ y, const float* __restrict__ tg
         const int x = (int)(v % g.W), yy = (int)((v / g.W) % g.H), z = (int)(v / ((long)g.W * g.H));
         const bool in = x < nx && yy < ny && z < nz;
         const long p = pidx(g, v);
-        for (int c = 0; c < COUT; ++c) {
-            bool ok = false;
-            if (c == 0) ok = in && x >= 1;
-            if (c == 1) ok = in && yy >= 1;
-            if (c == 2) ok = in && z >= 1;
-            float d = ok ? y[v * COUT + c] - tg[v * 4 + c] : 0.f;
+        const f4 a = *(const f4*)(y + v * COUT), b = *(const f4*)(tg + v * 4);
+        bf16_t o[COUT] = {};
+        for (int c = 0; c < 3; ++c) {
+            const bool ok = in && (c == 0 ? x : c == 1 ? yy : z) >= 1;
+            const float d = ok ? a[c] - b[c] : 0.f;
             acc += d * d;
-            gy[p * COUT + c] = f2bf(2.f * d * inv_n);
+            o[c] = f2bf(2.f * d * inv_n);
         }
+        for (int c = 0; c < COUT; c += 8) *(uint4*)(gy + p * COUT + c) = *(uint4*)(o + c);
     }
     s[threadIdx.x] = acc;
     __syncthreads();
@@ -823,7 +1005,7 @@ struct ep_net {
     float *w, *gr, *m, *v;     // FP32 masters, gradient, moments
     bf16_t *wb, *wtb;          // bf16 weights and transposed copies
     // activations
-    bf16_t *xin, *a0, *s0, *p0, *a1, *s1, *p1, *a2, *b2, *u1, *r6, *c1, *d1, *u0, *r8, *c0, *d0;
+    bf16_t *xin, *a0, *s0, *p0, *a1, *s1, *p1, *a2, *b2, *r6, *c1, *d1, *r8, *c0, *d0;
     float* y;
     // gradients
     bf16_t *gy, *z9, *gc0, *z8, *t0, *z7, *gc1, *z6, *t1, *z5, *z4, *t2, *z3, *z2, *t3, *z1, *z0;
@@ -910,10 +1092,10 @@ size_t net_carve(const ep_net_config* c, ep_net* n, char* base)
     float* v = (float*)take(np * 4);
     bf16_t* wb = (bf16_t*)take(nwb * 2);
     bf16_t* wtb = (bf16_t*)take(nwb * 2);
-    bf16_t* A[17];
-    const Vol* gl[17] = {&g0, &g0, &g0, &g1, &g1, &g1, &g2, &g2, &g2, &g1, &g1, &g1, &g1, &g0, &g0, &g0, &g0};
-    const int cl[17] = {CIN0, C, C, C, C2, C2, C2, C4, C4, C4, C2, C2, C2, C2, C, C, C};
-    for (int q = 0; q < 17; ++q) A[q] = act(*gl[q], cl[q]);
+    bf16_t* A[15];
+    const Vol* gl[15] = {&g0, &g0, &g0, &g1, &g1, &g1, &g2, &g2, &g2, &g1, &g1, &g1, &g0, &g0, &g0};
+    const int cl[15] = {CIN0, C, C, C, C2, C2, C2, C4, C4, C2, C2, C2, C, C, C};
+    for (int q = 0; q < 15; ++q) A[q] = act(*gl[q], cl[q]);
     float* y = (float*)take((size_t)g0.V * COUT * 4);
     bf16_t* G[17];
     const Vol* gg[17] = {&g0, &g0, &g0, &g0, &g0, &g1, &g1, &g1, &g1, &g2, &g2, &g2, &g1, &g1, &g1, &g0, &g0};
@@ -925,7 +1107,7 @@ size_t net_carve(const ep_net_config* c, ep_net* n, char* base)
     double* vlast = (double*)take((size_t)g0.V * 3 * 8);
     float* dvp = (float*)take((size_t)g0.V * 4 * 4);
     double* loss = (double*)take(8);
-    float* part = c->max_samples > 0 ? (float*)take(PART_FLOATS * 4) : nullptr;
+    float* part = c->max_samples > 0 ? (float*)take((PART_FLOATS + PART_BIAS * 128) * 4) : nullptr;
     if (n) {
         n->g[0] = g0; n->g[1] = g1; n->g[2] = g2;
         std::memcpy(n->ch, ch, sizeof(ch));
@@ -934,9 +1116,9 @@ size_t net_carve(const ep_net_config* c, ep_net* n, char* base)
         std::memcpy(n->wboff, wboff, sizeof(wboff));
         n->np = np; n->nwb = nwb;
         n->w = w; n->gr = gr; n->m = m; n->v = v; n->wb = wb; n->wtb = wtb;
-        bf16_t** dst[17] = {&n->xin, &n->a0, &n->s0, &n->p0, &n->a1, &n->s1, &n->p1, &n->a2, &n->b2,
-                            &n->u1, &n->r6, &n->c1, &n->d1, &n->u0, &n->r8, &n->c0, &n->d0};
-        for (int q = 0; q < 17; ++q) *dst[q] = A[q];
+        bf16_t** dst[15] = {&n->xin, &n->a0, &n->s0, &n->p0, &n->a1, &n->s1, &n->p1, &n->a2, &n->b2,
+                            &n->r6, &n->c1, &n->d1, &n->r8, &n->c0, &n->d0};
+        for (int q = 0; q < 15; ++q) *dst[q] = A[q];
         n->y = y;
         bf16_t** gd[17] = {&n->gy, &n->z9, &n->gc0, &n->z8, &n->t0, &n->z7, &n->gc1, &n->z6, &n->t1, &n->z5, &n->z4,
                            &n->t2, &n->z3, &n->z2, &n->t3, &n->z1, &n->z0};
@@ -985,50 +1167,44 @@ void conv(const ConvArgs& a, hipStream_t s)
     }
 }
 
-// Slabs of 128 voxels where neither tensor has more than 32 channels (fewer
-// barriers per voxel; the two stages still take only 17 KB of LDS), else 64.
-template <int NBO, int NBI>
-void launch_wgrad(unsigned grid, const bf16_t* X, const bf16_t* G, float* part, const Vol& g, long vchunk,
-                  hipStream_t s)
-{
-    constexpr int SL = (NBO <= 2 && NBI <= 2) ? 128 : 64;
-    k_wgrad<NBO, NBI, SL><<<grid, 256, 0, s>>>(X, G, part, g, vchunk);
-}
-
-template <int NBO>
-void wgrad_o(int nbi, const bf16_t* X, const bf16_t* G, float* part, float* dW, const Vol& g, hipStream_t s)
+// Weight and bias gradients of one layer through the partial-sum buffer,
+// deterministically.
+template <int CO, int CI, bool UP>
+void wgrad_block(WgradArgs a, float* dW, float* db, hipStream_t s)
 {
     // voxel chunks of at least 2048 voxels (a multiple of 128, so of either
-    // slab size), at most 512 per tap (27 x 512 workgroups keep the staging
-    // latency hidden) and as many as the partial-sum buffer holds
-    const long E = 27L * NBO * 16 * nbi * 16;
+    // slab size), at most 512 and as many as the partial-sum buffer holds
+    const Vol& g = a.g;
+    const long E = 27L * a.cout * a.cin;
     long nch = std::min<long>((g.V + 2047) / 2048, std::min<long>(512, PART_FLOATS / E));
-    const long vchunk = ((g.V + nch - 1) / nch + 127) / 128 * 128;
-    nch = (g.V + vchunk - 1) / vchunk;
-    const unsigned grid = (unsigned)nch * 27u;
-    switch (nbi) {
-    case 1: launch_wgrad<NBO, 1>(grid, X, G, part, g, vchunk, s); break;
-    case 2: launch_wgrad<NBO, 2>(grid, X, G, part, g, vchunk, s); break;
-    case 4: launch_wgrad<NBO, 4>(grid, X, G, part, g, vchunk, s); break;
-    default: launch_wgrad<NBO, 8>(grid, X, G, part, g, vchunk, s); break;
-    }
-    k_wsum<<<(unsigned)((E + 31) / 32), 256, 0, s>>>(part, nch, E, dW);
+    a.vchunk = ((g.V + nch - 1) / nch + 127) / 128 * 128;
+    a.nch = (int)((g.V + a.vchunk - 1) / a.vchunk);
+    a.nb = (int)std::min<long>(PART_BIAS, (g.V * (a.cout / 8) + 255) / 256);
+    k_bias_grad<<<(unsigned)a.nb, 256, 0, s>>>(a);
+    auto launch = [&](auto kernel, int co, int ci) {
+        const unsigned n = a.nch * (a.cout / (16 * co)) * (a.cin / (16 * ci));
+        kernel<<<n, 512 + WG_LOAD, 0, s>>>(a);
+        k_wsum<<<(unsigned)(E / 128 + a.cout), 256, 0, s>>>(a, E, co, ci, dW, db);
+    };
+    // Places of 32 voxels: their own, one per row and a row per plane more, and
+    // the taps' reach.  Rings of 512 places hold rows up to 157 voxels with 32
+    // input channels, of 1024 rows up to 328 with 16 (a workgroup per 16 input
+    // channels: 398 instead of 276 us of the layer above); with one ring per
+    // row offset a step loads three times as much.
+    const long span = 32 + (32 / g.W + 1) + (32 / ((long)g.W * g.H) + 1) * (g.W + 1) + 2L * (g.W + 2);
+    if (span <= 512) launch(k_wgrad<CO, CI, UP, 512, 1>, CO, CI);
+    else if (span <= 1024) launch(k_wgrad<CO, 1, UP, 1024, 1>, CO, 1);
+    else launch(k_wgrad<CO, 1, UP, 256, 3>, CO, 1);
 }
 
-// Weight and bias gradients of one layer, added to dW and db through the
-// partial-sum buffer part (PART_FLOATS floats), deterministically.
-void wgrad(float* part, int cout, int cin, const bf16_t* X, const bf16_t* G, float* dW, float* db, const Vol& g,
-           hipStream_t s)
+template <bool UP = false>
+void wgrad(const WgradArgs& a, float* dW, float* db, hipStream_t s)
 {
-    switch (cout / 16) {
-    case 1: wgrad_o<1>(cin / 16, X, G, part, dW, g, s); break;
-    case 2: wgrad_o<2>(cin / 16, X, G, part, dW, g, s); break;
-    case 4: wgrad_o<4>(cin / 16, X, G, part, dW, g, s); break;
-    default: wgrad_o<8>(cin / 16, X, G, part, dW, g, s); break;
-    }
-    const int nb = (int)std::min<long>(1024, (g.V * (cout / 8) + 255) / 256);
-    k_bias_grad<<<(unsigned)nb, 256, 0, s>>>(G, cout, part, g);
-    k_bsum<<<(unsigned)cout, 256, 0, s>>>(part, nb, cout, db);
+    // channel counts are 16 (the network's ends, and a base of 16) or multiples of 32
+    if (a.cout % 32 == 0 && a.cin % 32 == 0) wgrad_block<2, 2, UP>(a, dW, db, s);
+    else if (a.cout % 32 == 0) wgrad_block<2, 1, UP>(a, dW, db, s);
+    else if (a.cin % 32 == 0) wgrad_block<1, 2, UP>(a, dW, db, s);
+    else wgrad_block<1, 1, UP>(a, dW, db, s);
 }
 
 void refresh_bf16(ep_net* n)
@@ -1085,28 +1261,40 @@ void forward(ep_net* n, const bf16_t* x)
 }
 
 // Gradient of the loss of the current forward pass with respect to all
-// parameters, accumulated into n->gr (cleared first).
+// parameters, in n->gr.
 void backward(ep_net* n, const bf16_t* x)
 {
     hipStream_t s = n->st;
     const Vol &g0 = n->g[0], &g1 = n->g[1], &g2 = n->g[2];
     const int C = n->cfg.base, C2 = 2 * C, C4 = 4 * C;
-    auto weights = [&](int l, const bf16_t* X, const bf16_t* G, const Vol& g) {
-        wgrad(n->part, n->ch[l][1], n->ch[l][0], X, G, n->gr + n->woff[l], n->gr + n->boff[l], g, s);
+    auto args = [&](int l, const bf16_t* X, const bf16_t* G, const Vol& g, const Vol& gx) {
+        WgradArgs a{};
+        a.X = X;
+        a.G = G;
+        a.part = n->part;
+        a.bias = n->part + PART_FLOATS;
+        a.cin = n->ch[l][0];
+        a.cout = n->ch[l][1];
+        a.g = g;
+        a.gx = gx;
+        return a;
     };
-    k_fill_f<<<nblk(n->np), 256, 0, s>>>(n->gr, 0.f, n->np);
+    auto weights = [&](int l, const bf16_t* X, const bf16_t* G, const Vol& g) {
+        wgrad(args(l, X, G, g, g), n->gr + n->woff[l], n->gr + n->boff[l], s);
+    };
+    auto weights_up = [&](int l, const bf16_t* X, const bf16_t* G, const Vol& g, const Vol& parent) {
+        wgrad<true>(args(l, X, G, g, parent), n->gr + n->woff[l], n->gr + n->boff[l], s);
+    };
     weights(10, n->d0, n->gy, g0);
     layer<EPI_MASK>(n, 10, true, n->gy, n->z9, g0, n->d0);
     weights(9, n->c0, n->z9, g0);
     layer<EPI_LIN_MASK>(n, 9, true, n->z9, n->gc0, g0, n->r8, n->z8);
-    k_up<<<nblk(g0.V * (C2 / 8)), 256, 0, s>>>(n->d1, n->u0, C2, g0, g1);
-    weights(8, n->u0, n->z8, g0);
+    weights_up(8, n->d1, n->z8, g0, g1);
     layer<EPI_LIN>(n, 8, true, n->z8, n->t0, g0);
     k_up_dx<<<nblk(g1.V * (C2 / 8)), 256, 0, s>>>(n->t0, n->d1, n->z7, C2, g0, g1);
     weights(7, n->c1, n->z7, g1);
     layer<EPI_LIN_MASK>(n, 7, true, n->z7, n->gc1, g1, n->r6, n->z6);
-    k_up<<<nblk(g1.V * (C4 / 8)), 256, 0, s>>>(n->b2, n->u1, C4, g1, g2);
-    weights(6, n->u1, n->z6, g1);
+    weights_up(6, n->b2, n->z6, g1, g2);
     layer<EPI_LIN>(n, 6, true, n->z6, n->t1, g1);
     k_up_dx<<<nblk(g2.V * (C4 / 8)), 256, 0, s>>>(n->t1, n->b2, n->z5, C4, g1, g2);
     weights(5, n->a2, n->z5, g2);

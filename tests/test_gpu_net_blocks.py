@@ -1,8 +1,10 @@
-"""Convolution blocks of the warm-start network's kernels: the grids choose the
-blocks of 8 rows (32 and 16 output channels) and of 2 rows with 32 channels,
-each with ragged blocks in x, y and z; forward pass and gradients against the
-float64 oracle with the bars of test_gpu_net.py (2e-2 of the norm, every entry
-of a layer's gradient within 3e-2 of its largest)."""
+"""Blocks of the warm-start network's kernels.  The grids choose, in the
+convolutions, the blocks of 8 rows (32 and 16 output channels) and of 2 rows
+with 32 channels, each with ragged blocks in x, y and z, and, in the weight
+gradients, each kind of ring (rows up to 157, 328 and more voxels) and levels
+down to one voxel; forward pass and gradients against the float64 oracle with
+the bars of test_gpu_net.py (2e-2 of the norm, every entry of a layer's
+gradient within 3e-2 of its largest)."""
 import numpy as np
 import pytest
 
@@ -14,8 +16,9 @@ from test_gpu_net import net, random_net, rel, to_list
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("grid,base", [((70, 65, 66), 32), ((70, 65, 66), 16), ((45, 51, 46), 32)],
-                         ids=["8rows-32", "8rows-16", "2rows-32"])
+@pytest.mark.parametrize("grid,base", [((70, 65, 66), 32), ((70, 65, 66), 16), ((45, 51, 46), 32),
+                                       ((200, 6, 5), 32), ((341, 5, 9), 32), ((4, 4, 4), 16)],
+                         ids=["8rows-32", "8rows-16", "2rows-32", "rows-200", "rows-341", "one-voxel"])
 def test_forward_and_gradient_match_oracle(grid, base):
     say("net blocks", grid, base)
     n = net(*grid, base=base, samples=1)

@@ -50,8 +50,7 @@ typedef __attribute__((ext_vector_type(4))) float f4;
 constexpr int NL = 11;      // convolutions
 constexpr int CIN0 = 16;    // input channels (11 used)
 constexpr int COUT = 16;    // output channels (3 used)
-constexpr long PART_FLOATS = 1L << 23;   // partial-sum buffer of the parameter gradients (32 MiB)
-constexpr long PART_BIAS = 1024;         // workgroups of a bias gradient (behind it: their sums, 128 channels at most)
+constexpr long PART_FLOATS = 1L << 23;   // at most as many partial sums of a layer's weight gradient
 
 // ------------------------------------------------------------ bfloat16
 __device__ __forceinline__ float bf2f(bf16_t b) { return __uint_as_float((unsigned)b << 16); }
@@ -400,14 +399,31 @@ struct WgradArgs {
     float *part, *bias;                                      // partial sums: weights, bias
     int cin, cout;
     Vol g, gx;                                               // level of G; level of X (with UP the parent's)
-    long vchunk;
+    float *dW, *db;
+    long E, vchunk;                                          // weights; voxels of a chunk
     int nch, nb;                                             // chunks; workgroups for the bias
+    int co, ci, up, rows, wgs;                               // kernel: blocks of 16 channels, parent level, rings; its workgroups
 };
+// The layers of one launch: workgroups first[l] .. first[l + 1] - 1 are layer l's.
+struct WgradTable {
+    int n, first[NL + 1];
+    WgradArgs a[NL];
+};
+// the layer of this workgroup and the workgroup's number in it
+__device__ __forceinline__ int layer_of(const WgradTable& t, int& block)
+{
+    int l = 0;
+    while (l + 1 < t.n && (int)blockIdx.x >= t.first[l + 1]) ++l;
+    block = blockIdx.x - t.first[l];
+    return l;
+}
 
 // bias[block][c] = sum over the block's voxels of G[v][c] (k_wsum adds the
 // blocks up in a fixed order)
-__global__ __launch_bounds__(256) void k_bias_grad(WgradArgs a)
+__global__ __launch_bounds__(256) void k_bias_grad(WgradTable t)
 {
+    int block;
+    const WgradArgs& a = t.a[layer_of(t, block)];
     // thread = (voxel slot, group of 8 channels): 16-byte loads, a block
     // covers 256 / (C / 8) voxels per step (C in {16, 32, 64, 128})
     __shared__ float s[256 * 8];
@@ -415,7 +431,7 @@ __global__ __launch_bounds__(256) void k_bias_grad(WgradArgs a)
     const Vol& g = a.g;
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     const long step = (long)a.nb * nv;
-    long v = (long)blockIdx.x * nv + vq;
+    long v = (long)block * nv + vq;
     // 8 loads in flight: one after the other they took 37 us of a 32-channel
     // layer at 128^3
     for (; v + 7 * step < g.V; v += 8 * step) {
@@ -439,9 +455,15 @@ __global__ __launch_bounds__(256) void k_bias_grad(WgradArgs a)
         const int gq = threadIdx.x / 8, k = threadIdx.x % 8;
         float sum = 0.f;
         for (int q = 0; q < nv; ++q) sum += s[(q * ng + gq) * 8 + k];
-        a.bias[(long)blockIdx.x * C + threadIdx.x] = sum;
+        a.bias[(long)block * C + threadIdx.x] = sum;
     }
 }
+
+// of two steps: the voxels' places (in elements); blocks of 32 voxels, whether
+// the next step is stored after it, whether there is one
+struct WgradSteps {
+    int place[2][WG_STEP], blocks[2], wait[2], more[2];
+};
 
 // part[chunk][group][block pair][tap][lane][4]: sum over the chunk's voxels of
 // G[v][o] X[v + off_t][i], for groups of 16 CO output and 16 CI input
@@ -465,11 +487,12 @@ __global__ __launch_bounds__(256) void k_bias_grad(WgradArgs a)
 // pitch measured) and the instructions of the loading waves.  With a
 // workgroup per tap and chunk, which staged both tensors transposed 27 times,
 // the eleven layers of a gradient at 128^3 with 32 base channels took 5.9 ms,
-// at 72 x 64 x 48 with 16 0.55 ms; they take 1.9 and 0.37.  32 -> 32 channels
-// at 128^3: 276 us, of the 46 that its products take.  Loading from the
-// computing waves themselves: 384 us (9 windows per step) and 519 (rings).
+// at 72 x 64 x 48 with 16 0.55 ms; they take 1.65 and 0.10 in one launch (1.9
+// and 0.37 in eleven).  32 -> 32 channels at 128^3 alone: 276 us, of the 46
+// that its products take.  Loading from the computing waves themselves: 384 us
+// (9 windows per step) and 519 (rings).
 template <int CO, int CI, bool UP, int R, int ROWS>
-__global__ __launch_bounds__(512 + WG_LOAD, 3) void k_wgrad(WgradArgs a)
+__device__ __forceinline__ void wgrad_chunk(const WgradArgs& a, int block, bf16_t* lds, WgradSteps& steps)
 {
     constexpr int NO = CO * 16, NI = CI * 16;                // channels
     constexpr int TG = 8 / CI, PER = (27 + TG - 1) / TG;     // waves that share the taps, taps of a wave
@@ -477,13 +500,10 @@ __global__ __launch_bounds__(512 + WG_LOAD, 3) void k_wgrad(WgradArgs a)
     constexpr int NEW = WG_NEW, NP = NI / 8;                 // 16-byte pieces of a voxel
     constexpr int PX = (ROWS * NEW * NP + WG_LOAD - 1) / WG_LOAD, PG = GE / 8 / WG_LOAD;    // per loading thread
     static_assert(GE / 8 % WG_LOAD == 0, "");
-    __shared__ __attribute__((aligned(16))) bf16_t lds[XE + 2 * GE];
-    // of two steps: the voxels' places (in elements); blocks of 32 voxels, whether
-    // the next step is stored after it, whether there is one
-    __shared__ int place[2][WG_STEP], blocks[2], wait[2], more[2];
+    auto& [place, blocks, wait, more] = steps;
     const Vol &g = a.g, &gx = a.gx;
     const int ngi = a.cin / NI, ng = ngi * (a.cout / NO), nw = a.nch * ng;
-    const int lb = xcd_order(blockIdx.x, nw), chunk = lb / ng, grp = lb % ng;
+    const int lb = xcd_order(block, nw), chunk = lb / ng, grp = lb % ng;
     const int o0 = grp / ngi * NO, i0 = grp % ngi * NI;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int W1 = g.W + 1;
@@ -698,6 +718,25 @@ __global__ __launch_bounds__(512 + WG_LOAD, 3) void k_wgrad(WgradArgs a)
     }
 }
 
+// The weight gradients of all layers of one kind of ring in one launch: one
+// layer's chunks do not fill the chip evenly (303 workgroups at 128^3, 14 of
+// the middle level at 72 x 64 x 48).
+template <int CI, int R, int ROWS>
+__global__ __launch_bounds__(512 + WG_LOAD, 3) void k_wgrad(WgradTable t)
+{
+    __shared__ __attribute__((aligned(16))) bf16_t lds[3 * ROWS * R * CI * 16 + 2 * WG_STEP * 32];
+    __shared__ WgradSteps steps;
+    int block;
+    const WgradArgs& a = t.a[layer_of(t, block)];
+    if (a.co == 2) {
+        if (a.up) wgrad_chunk<2, CI, true, R, ROWS>(a, block, lds, steps);
+        else wgrad_chunk<2, CI, false, R, ROWS>(a, block, lds, steps);
+    } else {
+        if (a.up) wgrad_chunk<1, CI, true, R, ROWS>(a, block, lds, steps);
+        else wgrad_chunk<1, CI, false, R, ROWS>(a, block, lds, steps);
+    }
+}
+
 // dW and db = sums over the chunks' and the bias blocks' partial sums in a
 // fixed order.  Weights: E / 128 workgroups of 32 groups of 4 entries, thread
 // j of 8 sums chunks j, j + 8, ..., then the eight sums are added in j order;
@@ -705,14 +744,16 @@ __global__ __launch_bounds__(512 + WG_LOAD, 3) void k_wgrad(WgradArgs a)
 // input channel lane % 16 of its block.  Bias: one workgroup per channel,
 // thread j sums blocks j, j + 256, ..., then a tree of fixed shape adds the
 // 256 sums.
-__global__ __launch_bounds__(256) void k_wsum(WgradArgs a, long E, int co, int ci, float* __restrict__ dW,
-                                              float* __restrict__ db)
+__global__ __launch_bounds__(256) void k_wsum(WgradTable table)
 {
     __shared__ f4 s[8][32];
-    const long nw = E / 128;
-    if (blockIdx.x >= nw) {
+    int block;
+    const WgradArgs& a = table.a[layer_of(table, block)];
+    const long E = a.E, nw = E / 128;
+    const int co = a.co, ci = a.ci;
+    if (block >= nw) {
         float* const t = (float*)s;
-        const int c = (int)(blockIdx.x - nw);
+        const int c = (int)(block - nw);
         float acc = 0.f;
         for (int b = threadIdx.x; b < a.nb; b += 256) acc += a.bias[(long)b * a.cout + c];
         t[threadIdx.x] = acc;
@@ -721,11 +762,11 @@ __global__ __launch_bounds__(256) void k_wsum(WgradArgs a, long E, int co, int c
             if ((int)threadIdx.x < w) t[threadIdx.x] += t[threadIdx.x + w];
             __syncthreads();
         }
-        if (threadIdx.x == 0) db[c] = t[0];
+        if (threadIdx.x == 0) a.db[c] = t[0];
         return;
     }
     const int el = threadIdx.x & 31, jl = threadIdx.x >> 5;
-    const long e = blockIdx.x * 128L + el * 4;
+    const long e = block * 128L + el * 4;
     f4 sum{0.f, 0.f, 0.f, 0.f};
     auto add = [&](const f4& v) {
 #pragma unroll
@@ -742,7 +783,7 @@ __global__ __launch_bounds__(256) void k_wsum(WgradArgs a, long E, int co, int c
     const int o = (grp / ngi * co + pair / ci) * 16 + lane / 16 * 4;
     const int i = (grp % ngi * ci + pair % ci) * 16 + lane % 16;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) dW[((long)(o + k) * 27 + t) * a.cin + i] = sum[k];
+    for (int k = 0; k < 4; ++k) a.dW[((long)(o + k) * 27 + t) * a.cin + i] = sum[k];
 }
 
 // ------------------------------------------------------------ elementwise
@@ -898,17 +939,25 @@ __global__ void k_adam(float* __restrict__ w, const float* __restrict__ gr, floa
     w[e] -= lr * (mm / c1) / (sqrtf(v2 / c2) + eps);
 }
 
-// bfloat16 copies of one layer's weights for its convolution and, transposed
-// and tap-mirrored, for the one of its input gradient, both in the order in
-// which the convolution's waves load them (weight_at).
-__global__ void k_wcopy(const float* __restrict__ w, bf16_t* __restrict__ wb, bf16_t* __restrict__ wtb, int co, int ci)
+// bfloat16 copies of all layers' weights for their convolutions and,
+// transposed and tap-mirrored, for those of their input gradients, both in the
+// order in which the convolution's waves load them (weight_at).
+struct WcopyTable {
+    long first[NL + 1], woff[NL], wboff[NL];                 // first entry, place in the parameters and in the copies
+    int co[NL], ci[NL];
+};
+__global__ void k_wcopy(WcopyTable t, const float* __restrict__ w, bf16_t* __restrict__ wb, bf16_t* __restrict__ wtb)
 {
-    const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (long)co * 27 * ci) return;
-    const int i = (int)(e % ci), t = (int)((e / ci) % 27), o = (int)(e / ((long)ci * 27));
-    const bf16_t b = f2bf(w[e]);
-    wb[weight_at(o, t, i, ci, co)] = b;
-    wtb[weight_at(i, 26 - t, o, co, ci)] = b;
+    const long at = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (at >= t.first[NL]) return;
+    int l = 0;
+    while (at >= t.first[l + 1]) ++l;
+    const long e = at - t.first[l];
+    const int ci = t.ci[l], co = t.co[l];
+    const int i = (int)(e % ci), tap = (int)((e / ci) % 27), o = (int)(e / ((long)ci * 27));
+    const bf16_t b = f2bf(w[t.woff[l] + e]);
+    wb[t.wboff[l] + weight_at(o, tap, i, ci, co)] = b;
+    wtb[t.wboff[l] + weight_at(i, 26 - tap, o, co, ci)] = b;
 }
 
 // ------------------------------------------------------------ solver side
@@ -1060,6 +1109,33 @@ void layer_channels(int base, int ch[NL][2])
     std::memcpy(ch, t, sizeof(t));
 }
 
+// Weight gradient l of level g: chunks, partial sums and kernel.
+WgradArgs wgrad_plan(int cout, int cin, const Vol& g)
+{
+    // voxel chunks of at least 2048 voxels (a multiple of 128), at most 512
+    // and as many as PART_FLOATS partial sums hold
+    WgradArgs a{};
+    a.cin = cin;
+    a.cout = cout;
+    a.g = g;
+    a.E = 27L * cout * cin;
+    long nch = std::min<long>((g.V + 2047) / 2048, std::min<long>(512, PART_FLOATS / a.E));
+    a.vchunk = ((g.V + nch - 1) / nch + 127) / 128 * 128;
+    a.nch = (int)((g.V + a.vchunk - 1) / a.vchunk);
+    a.nb = (int)std::min<long>(1024, (g.V * (cout / 8) + 255) / 256);
+    // Places of 32 voxels: their own, one per row and a row per plane more, and
+    // the taps' reach.  Rings of 512 places hold rows up to 157 voxels with 32
+    // input channels, of 1024 rows up to 328 with 16 (a workgroup per 16 input
+    // channels: 398 instead of 276 us of a 32 -> 32 channel layer at 128^3);
+    // with one ring per row offset a step loads three times as much.
+    const long span = 32 + (32 / g.W + 1) + (32 / ((long)g.W * g.H) + 1) * (g.W + 1) + 2L * (g.W + 2);
+    a.rows = span <= 512 ? 0 : span <= 1024 ? 1 : 2;
+    a.co = cout % 32 == 0 ? 2 : 1;                           // channel counts are 16 or multiples of 32
+    a.ci = a.rows == 0 && cin % 32 == 0 ? 2 : 1;
+    a.wgs = a.nch * (cout / (16 * a.co)) * (cin / (16 * a.ci));
+    return a;
+}
+
 // Walk the workspace layout (assign pointers when n->... base != null).
 size_t net_carve(const ep_net_config* c, ep_net* n, char* base)
 {
@@ -1107,7 +1183,14 @@ size_t net_carve(const ep_net_config* c, ep_net* n, char* base)
     double* vlast = (double*)take((size_t)g0.V * 3 * 8);
     float* dvp = (float*)take((size_t)g0.V * 4 * 4);
     double* loss = (double*)take(8);
-    float* part = c->max_samples > 0 ? (float*)take((PART_FLOATS + PART_BIAS * 128) * 4) : nullptr;
+    // partial sums of the parameter gradients (k_loss's before them)
+    long sums = 2 * 1024;
+    const Vol* lv[NL] = {&g0, &g0, &g1, &g1, &g2, &g2, &g1, &g1, &g0, &g0, &g0};
+    for (int l = 0; l < NL; ++l) {
+        const WgradArgs a = wgrad_plan(ch[l][1], ch[l][0], *lv[l]);
+        sums += a.nch * a.E + (long)a.nb * a.cout;
+    }
+    float* part = c->max_samples > 0 ? (float*)take(sums * 4) : nullptr;
     if (n) {
         n->g[0] = g0; n->g[1] = g1; n->g[2] = g2;
         std::memcpy(n->ch, ch, sizeof(ch));
@@ -1167,53 +1250,43 @@ void conv(const ConvArgs& a, hipStream_t s)
     }
 }
 
-// Weight and bias gradients of one layer through the partial-sum buffer,
-// deterministically.
-template <int CO, int CI, bool UP>
-void wgrad_block(WgradArgs a, float* dW, float* db, hipStream_t s)
+// Weight and bias gradients of all layers, deterministically: the partial sums
+// of each kind of ring, the layers with the longest chunks first, then the sums.
+void wgrad(const WgradArgs (&layers)[NL], hipStream_t s)
 {
-    // voxel chunks of at least 2048 voxels (a multiple of 128, so of either
-    // slab size), at most 512 and as many as the partial-sum buffer holds
-    const Vol& g = a.g;
-    const long E = 27L * a.cout * a.cin;
-    long nch = std::min<long>((g.V + 2047) / 2048, std::min<long>(512, PART_FLOATS / E));
-    a.vchunk = ((g.V + nch - 1) / nch + 127) / 128 * 128;
-    a.nch = (int)((g.V + a.vchunk - 1) / a.vchunk);
-    a.nb = (int)std::min<long>(PART_BIAS, (g.V * (a.cout / 8) + 255) / 256);
-    k_bias_grad<<<(unsigned)a.nb, 256, 0, s>>>(a);
-    auto launch = [&](auto kernel, int co, int ci) {
-        const unsigned n = a.nch * (a.cout / (16 * co)) * (a.cin / (16 * ci));
-        kernel<<<n, 512 + WG_LOAD, 0, s>>>(a);
-        k_wsum<<<(unsigned)(E / 128 + a.cout), 256, 0, s>>>(a, E, co, ci, dW, db);
+    auto table = [&](auto&& wgs) {
+        WgradTable t{};
+        for (const WgradArgs& a : layers)
+            if (wgs(a) > 0) t.a[t.n++] = a;
+        std::stable_sort(t.a, t.a + t.n, [](const WgradArgs& p, const WgradArgs& q) { return p.vchunk > q.vchunk; });
+        for (int l = 0; l < t.n; ++l) t.first[l + 1] = t.first[l] + wgs(t.a[l]);
+        return t;
     };
-    // Places of 32 voxels: their own, one per row and a row per plane more, and
-    // the taps' reach.  Rings of 512 places hold rows up to 157 voxels with 32
-    // input channels, of 1024 rows up to 328 with 16 (a workgroup per 16 input
-    // channels: 398 instead of 276 us of the layer above); with one ring per
-    // row offset a step loads three times as much.
-    const long span = 32 + (32 / g.W + 1) + (32 / ((long)g.W * g.H) + 1) * (g.W + 1) + 2L * (g.W + 2);
-    if (span <= 512) launch(k_wgrad<CO, CI, UP, 512, 1>, CO, CI);
-    else if (span <= 1024) launch(k_wgrad<CO, 1, UP, 1024, 1>, CO, 1);
-    else launch(k_wgrad<CO, 1, UP, 256, 3>, CO, 1);
-}
-
-template <bool UP = false>
-void wgrad(const WgradArgs& a, float* dW, float* db, hipStream_t s)
-{
-    // channel counts are 16 (the network's ends, and a base of 16) or multiples of 32
-    if (a.cout % 32 == 0 && a.cin % 32 == 0) wgrad_block<2, 2, UP>(a, dW, db, s);
-    else if (a.cout % 32 == 0) wgrad_block<2, 1, UP>(a, dW, db, s);
-    else if (a.cin % 32 == 0) wgrad_block<1, 2, UP>(a, dW, db, s);
-    else wgrad_block<1, 1, UP>(a, dW, db, s);
+    auto launch = [&](auto kernel, const WgradTable& t, int threads) {
+        if (t.n) kernel<<<(unsigned)t.first[t.n], threads, 0, s>>>(t);
+    };
+    auto kind = [&](int ci, int rows) {
+        return table([=](const WgradArgs& a) { return a.ci == ci && a.rows == rows ? a.wgs : 0; });
+    };
+    launch(k_bias_grad, table([](const WgradArgs& a) { return a.nb; }), 256);
+    launch(k_wgrad<2, 512, 1>, kind(2, 0), 512 + WG_LOAD);
+    launch(k_wgrad<1, 512, 1>, kind(1, 0), 512 + WG_LOAD);
+    launch(k_wgrad<1, 1024, 1>, kind(1, 1), 512 + WG_LOAD);
+    launch(k_wgrad<1, 256, 3>, kind(1, 2), 512 + WG_LOAD);
+    launch(k_wsum, table([](const WgradArgs& a) { return (int)(a.E / 128) + a.cout; }), 256);
 }
 
 void refresh_bf16(ep_net* n)
 {
+    WcopyTable t{};
     for (int l = 0; l < NL; ++l) {
-        const long cnt = (long)n->ch[l][1] * 27 * n->ch[l][0];
-        k_wcopy<<<nblk(cnt), 256, 0, n->st>>>(n->w + n->woff[l], n->wb + n->wboff[l], n->wtb + n->wboff[l],
-                                              n->ch[l][1], n->ch[l][0]);
+        t.first[l + 1] = t.first[l] + (long)n->ch[l][1] * 27 * n->ch[l][0];
+        t.woff[l] = n->woff[l];
+        t.wboff[l] = n->wboff[l];
+        t.co[l] = n->ch[l][1];
+        t.ci[l] = n->ch[l][0];
     }
+    k_wcopy<<<nblk(t.first[NL]), 256, 0, n->st>>>(t, n->w, n->wb, n->wtb);
 }
 
 const bf16_t* slot_x(const ep_net* n, int slot) { return slot < 0 ? n->xin : n->sx + (size_t)slot * n->g[0].Vp * 16; }
@@ -1267,34 +1340,32 @@ void backward(ep_net* n, const bf16_t* x)
     hipStream_t s = n->st;
     const Vol &g0 = n->g[0], &g1 = n->g[1], &g2 = n->g[2];
     const int C = n->cfg.base, C2 = 2 * C, C4 = 4 * C;
-    auto args = [&](int l, const bf16_t* X, const bf16_t* G, const Vol& g, const Vol& gx) {
-        WgradArgs a{};
+    // layer l's gradients from its input X and output gradient G, which both
+    // stay until all are known
+    WgradArgs grads[NL];
+    float* part = n->part;
+    auto weights = [&](int l, const bf16_t* X, const bf16_t* G, const Vol& g, const Vol* parent = nullptr) {
+        WgradArgs& a = grads[l] = wgrad_plan(n->ch[l][1], n->ch[l][0], g);
         a.X = X;
         a.G = G;
-        a.part = n->part;
-        a.bias = n->part + PART_FLOATS;
-        a.cin = n->ch[l][0];
-        a.cout = n->ch[l][1];
-        a.g = g;
-        a.gx = gx;
-        return a;
-    };
-    auto weights = [&](int l, const bf16_t* X, const bf16_t* G, const Vol& g) {
-        wgrad(args(l, X, G, g, g), n->gr + n->woff[l], n->gr + n->boff[l], s);
-    };
-    auto weights_up = [&](int l, const bf16_t* X, const bf16_t* G, const Vol& g, const Vol& parent) {
-        wgrad<true>(args(l, X, G, g, parent), n->gr + n->woff[l], n->gr + n->boff[l], s);
+        a.gx = parent ? *parent : g;
+        a.up = parent != nullptr;
+        a.part = part;
+        a.bias = part += a.nch * a.E;
+        part += (long)a.nb * a.cout;
+        a.dW = n->gr + n->woff[l];
+        a.db = n->gr + n->boff[l];
     };
     weights(10, n->d0, n->gy, g0);
     layer<EPI_MASK>(n, 10, true, n->gy, n->z9, g0, n->d0);
     weights(9, n->c0, n->z9, g0);
     layer<EPI_LIN_MASK>(n, 9, true, n->z9, n->gc0, g0, n->r8, n->z8);
-    weights_up(8, n->d1, n->z8, g0, g1);
+    weights(8, n->d1, n->z8, g0, &g1);
     layer<EPI_LIN>(n, 8, true, n->z8, n->t0, g0);
     k_up_dx<<<nblk(g1.V * (C2 / 8)), 256, 0, s>>>(n->t0, n->d1, n->z7, C2, g0, g1);
     weights(7, n->c1, n->z7, g1);
     layer<EPI_LIN_MASK>(n, 7, true, n->z7, n->gc1, g1, n->r6, n->z6);
-    weights_up(6, n->b2, n->z6, g1, g2);
+    weights(6, n->b2, n->z6, g1, &g2);
     layer<EPI_LIN>(n, 6, true, n->z6, n->t1, g1);
     k_up_dx<<<nblk(g2.V * (C4 / 8)), 256, 0, s>>>(n->t1, n->b2, n->z5, C4, g1, g2);
     weights(5, n->a2, n->z5, g2);
@@ -1310,6 +1381,7 @@ void backward(ep_net* n, const bf16_t* x)
     weights(1, n->a0, n->z1, g0);
     layer<EPI_MASK>(n, 1, true, n->z1, n->z0, g0, n->a0);
     weights(0, x, n->z0, g0);
+    wgrad(grads, s);
 }
 
 float inv_count(const ep_net* n)

@@ -385,15 +385,20 @@ __device__ __forceinline__ b8 ld_tr(const bf16_t* p, const bf16_t* q)
 }
 __device__ __forceinline__ int div_by(int n, float inv) { return (int)(((float)n + 0.5f) * inv); }   // n < 2^22
 
-// n / d of values that are the same in all lanes, most often 0 (an integer
-// division is some 40 dependent instructions)
+// n / d of values that are the same in all lanes, most often 0 or 1 (an
+// integer division is some 40 dependent instructions)
 __device__ __forceinline__ int div_uniform(int n, int d, float inv)
 {
-    return n < d ? 0 : __builtin_amdgcn_readfirstlane(div_by(n, inv));
+    if (n < d) return 0;
+    if (n < 2 * d) return 1;
+    return __builtin_amdgcn_readfirstlane(div_by(n, inv));
 }
 
 constexpr int WG_STEP = 128, WG_NEW = 192;                   // voxels of a step, new places of one load
 constexpr int WG_LOAD = 256;                                 // threads that load (behind 512 that compute)
+// with 32 input channels others load G (1.41 instead of 1.54 ms for the layers
+// of a gradient at 128^3; with 16, two workgroups per CU, 0.13 instead of 0.11)
+constexpr int wg_threads(int ci) { return 512 + ci * WG_LOAD; }
 struct WgradArgs {
     const bf16_t *X, *G;
     float *part, *bias;                                      // partial sums: weights, bias
@@ -401,7 +406,7 @@ struct WgradArgs {
     Vol g, gx;                                               // level of G; level of X (with UP the parent's)
     float *dW, *db;
     long E, vchunk;                                          // weights; voxels of a chunk
-    int nch, nb;                                             // chunks; workgroups for the bias
+    int nch, nb, step;                                       // chunks; workgroups for the bias; voxels of a step at most
     int co, ci, up, rows, wgs;                               // kernel: blocks of 16 channels, parent level, rings; its workgroups
 };
 // The layers of one launch: workgroups first[l] .. first[l + 1] - 1 are layer l's.
@@ -478,16 +483,16 @@ struct WgradSteps {
 // them.  (Rows too long for a ring: ROWS = 3 rings per plane, one per dy, and
 // no row between planes.)  Eight waves compute: they share the (input block,
 // tap) pairs, each with all output blocks, so that a fragment of X is read
-// once.  Four waves load: while a step is computed they store the next one's
-// voxels and the list of its places to LDS and fetch the voxels of the one
-// after it into registers.
+// once.  Four waves load (eight with CI = 2): while a step is computed they store the
+// next one's voxels and the list of its places to LDS and fetch the voxels of
+// the one after it into registers.
 //
 // What bounds it: LDS reads (a fragment of 1 KB takes 10 clocks of the CU and
 // serves CO products of 4 each; their banks do not conflict at any voxel
 // pitch measured) and the instructions of the loading waves.  With a
 // workgroup per tap and chunk, which staged both tensors transposed 27 times,
 // the eleven layers of a gradient at 128^3 with 32 base channels took 5.9 ms,
-// at 72 x 64 x 48 with 16 0.55 ms; they take 1.65 and 0.10 in one launch (1.9
+// at 72 x 64 x 48 with 16 0.55 ms; they take 1.53 and 0.10 in one launch (1.9
 // and 0.37 in eleven).  32 -> 32 channels at 128^3 alone: 276 us, of the 46
 // that its products take.  Loading from the computing waves themselves: 384 us
 // (9 windows per step) and 519 (rings).
@@ -507,7 +512,7 @@ __device__ __forceinline__ void wgrad_chunk(const WgradArgs& a, int block, bf16_
     const int o0 = grp / ngi * NO, i0 = grp % ngi * NI;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int W1 = g.W + 1;
-    const int loader = tid - 512;
+    const int loader = tid < 512 ? -1 : (tid - 512) % WG_LOAD;
     if (loader < 0) {
         const int l0 = (lane >> 4) * 8 + (lane & 15) / 4, c4 = lane % 4 * 4;   // voxel and channels the lane reads
         const int ib = wave % CI, tg = wave / CI, mine = ib * 16 + c4;
@@ -662,67 +667,86 @@ __device__ __forceinline__ void wgrad_chunk(const WgradArgs& a, int block, bf16_
             vg[u] = read(rs, v.z + plane < g.D ? (unsigned)(((plane * g.Hp + y - v.y) * g.Wp + x) * a.cout) * 2u + gp * 16 : NONE);
         }
     };
-    // A step has as many voxels, up to 128, as have room in the ring beside the
+    // A step has as many voxels, up to a.step, as have room in the ring beside the
     // step before it; where not even 32 have, the step before it is done
     // first.  It is fetched ahead unless it brings too many places for one load
     // (at a chunk's start, or where it crosses planes).
     long left = v1 - v0;
     int voxels, end;                                         // of the step from v on; end of its places
+    bool held = false;                                       // no room in the ring until the step before it is computed
     auto size = [&](int first) {
-        for (voxels = WG_STEP;; voxels -= 32) {
+        for (voxels = a.step;; voxels -= 32) {
             end = ahead_of(v, voxels - 1).q + reach + 1;
             if (end - first <= R || voxels == 32) return;
         }
     };
-    size(v.q - reach);
-    bool fetched = false;
-    for (int b = 0;; b ^= 1) {
-        if (!fetched) {
-            while (end - n.q > NEW) {
-                load_x(NEW);
-                store_x(NEW);
-            }
-            load_x(end - n.q);
-            load_g();
-        }
-        store_x(end - n.q);
-#pragma unroll
-        for (int u = 0; u < PG; ++u) *(uint4*)(lds + XE + b * GE + (loader + WG_LOAD * u) * 8) = vg[u];
-        if (loader < WG_STEP) {
-            const int run = div_by(v.x + loader, inv_w), plane = div_by(v.y + run, inv_h);
-            place[b][loader] = (v.q + loader + run + plane * gap) * NI;
-        }
-        // the chunk's last step may be shorter (behind the volume G is 0)
-        const int first = v.q - reach, kb = left < voxels ? (int)(left + 31) / 32 : voxels / 32;
+    auto advance = [&] {                                     // to the next step, if there is one
+        const int first = v.q - reach;
         left -= voxels;
-        const bool go_on = left > 0;
-        bool held = false;
-        if (go_on) {
-            v = ahead_of(v, voxels);
-            size(first);
-            held = end - first > R;                          // no room in the ring until this step is computed
-            fetched = end - n.q <= NEW;
-            if (fetched) {
-                load_x(end - n.q);
-                load_g();
+        held = false;
+        if (left <= 0) return false;
+        v = ahead_of(v, voxels);
+        size(first);
+        held = end - first > R;
+        return true;
+    };
+    size(v.q - reach);
+    // one loop per kind of loading wave: the compiler then knows which loads
+    // are in flight when it waits for one
+    auto load = [&](auto does_x, auto does_g) {
+        if (does_g) load_g();
+        bool fetched = false;                                // X
+        for (int b = 0;; b ^= 1) {
+            if (does_x) {
+                if (!fetched) {
+                    while (end - n.q > NEW) {
+                        load_x(NEW);
+                        store_x(NEW);
+                    }
+                    load_x(end - n.q);
+                }
+                store_x(end - n.q);
             }
+            if (does_g) {
+#pragma unroll
+                for (int u = 0; u < PG; ++u) *(uint4*)(lds + XE + b * GE + (loader + WG_LOAD * u) * 8) = vg[u];
+                if (loader < WG_STEP) {
+                    const int run = div_by(v.x + loader, inv_w), plane = div_by(v.y + run, inv_h);
+                    place[b][loader] = (v.q + loader + run + plane * gap) * NI;
+                }
+            }
+            // the chunk's last step may be shorter (behind the volume G is 0)
+            const int kb = left < voxels ? (int)(left + 31) / 32 : voxels / 32;
+            const bool go_on = advance();
+            if (does_x) {
+                fetched = go_on && end - n.q <= NEW;
+                if (fetched) load_x(end - n.q);
+            }
+            if (does_g) {
+                if (go_on) load_g();
+                if (loader == 0) {
+                    blocks[b] = kb;
+                    wait[b] = held;
+                    more[b] = go_on;
+                }
+            }
+            __syncthreads();
+            if (held) __syncthreads();
+            if (!go_on) return;
         }
-        if (loader == 0) {
-            blocks[b] = kb;
-            wait[b] = held;
-            more[b] = go_on;
-        }
-        __syncthreads();
-        if (held) __syncthreads();
-        if (!go_on) return;
-    }
+    };
+    using T = std::true_type;
+    using F = std::false_type;
+    if constexpr (CI == 1) load(T(), T());
+    else if (tid < 512 + WG_LOAD) load(T(), F());
+    else load(F(), T());
 }
 
 // The weight gradients of all layers of one kind of ring in one launch: one
 // layer's chunks do not fill the chip evenly (303 workgroups at 128^3, 14 of
 // the middle level at 72 x 64 x 48).
 template <int CI, int R, int ROWS>
-__global__ __launch_bounds__(512 + WG_LOAD, 3) void k_wgrad(WgradTable t)
+__global__ __launch_bounds__(wg_threads(CI), 2 + CI) void k_wgrad(WgradTable t)
 {
     __shared__ __attribute__((aligned(16))) bf16_t lds[3 * ROWS * R * CI * 16 + 2 * WG_STEP * 32];
     __shared__ WgradSteps steps;
@@ -1130,6 +1154,9 @@ WgradArgs wgrad_plan(int cout, int cin, const Vol& g)
     // with one ring per row offset a step loads three times as much.
     const long span = 32 + (32 / g.W + 1) + (32 / ((long)g.W * g.H) + 1) * (g.W + 1) + 2L * (g.W + 2);
     a.rows = span <= 512 ? 0 : span <= 1024 ? 1 : 2;
+    // two steps inside a plane beside each other in a ring
+    const long ring = a.rows == 0 ? 512 : a.rows == 1 ? 1024 : 256, reach = a.rows == 2 ? 2 : 2L * (g.W + 2);
+    for (a.step = WG_STEP; a.step > 32 && 2 * a.step + 2 * a.step / g.W + 1 + reach > ring;) a.step -= 32;
     a.co = cout % 32 == 0 ? 2 : 1;                           // channel counts are 16 or multiples of 32
     a.ci = a.rows == 0 && cin % 32 == 0 ? 2 : 1;
     a.wgs = a.nch * (cout / (16 * a.co)) * (cin / (16 * a.ci));
@@ -1269,10 +1296,10 @@ void wgrad(const WgradArgs (&layers)[NL], hipStream_t s)
         return table([=](const WgradArgs& a) { return a.ci == ci && a.rows == rows ? a.wgs : 0; });
     };
     launch(k_bias_grad, table([](const WgradArgs& a) { return a.nb; }), 256);
-    launch(k_wgrad<2, 512, 1>, kind(2, 0), 512 + WG_LOAD);
-    launch(k_wgrad<1, 512, 1>, kind(1, 0), 512 + WG_LOAD);
-    launch(k_wgrad<1, 1024, 1>, kind(1, 1), 512 + WG_LOAD);
-    launch(k_wgrad<1, 256, 3>, kind(1, 2), 512 + WG_LOAD);
+    launch(k_wgrad<2, 512, 1>, kind(2, 0), wg_threads(2));
+    launch(k_wgrad<1, 512, 1>, kind(1, 0), wg_threads(1));
+    launch(k_wgrad<1, 1024, 1>, kind(1, 1), wg_threads(1));
+    launch(k_wgrad<1, 256, 3>, kind(1, 2), wg_threads(1));
     launch(k_wsum, table([](const WgradArgs& a) { return (int)(a.E / 128) + a.cout; }), 256);
 }
 

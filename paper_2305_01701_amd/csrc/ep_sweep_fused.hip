@@ -582,7 +582,10 @@ bool fused_preferred(int, bool) { return true; }
 // chunk length: the choice is within 4 % (FP32) and 6 % (FP64) of the best
 // of them, 1 % on average.  FP64 chunks of 64 planes only where a plane has
 // at most 1 MB: 255^3 0.81 against 0.85 ms in chunks of 32, but 511^3 7.75
-// against 6.59 ms in chunks of 43.
+// against 6.59 ms in chunks of 43.  The small FP32 tiles read 1.9 values per
+// point, which at 5.1 TB/s takes longer than their march where they fill the
+// chip (500 x 500 x 8: 79 us, 32 x 16 tiles 63; with a per-cell G and 12
+// planes 150 and 106).
 FusedPlan fused_plan_3d(bool fp32, bool has_g, int nx, int ny, int nz, long sz)
 {
     static const int cus = device_cus();
@@ -609,7 +612,13 @@ FusedPlan fused_plan_3d(bool fp32, bool has_g, int nx, int ny, int nz, long sz)
                 if (rounds > 0.0) last = last * (1.0 - overlap) + c[q].full * overlap * rest / (cus * c[q].res);
                 step += last;
             }
-            const double t = c[q].launch + (zc + 3) * step;
+            double t = c[q].launch + (zc + 3) * step;
+            // full rounds of the small FP32 tiles are bound by their halo's bytes
+            if (fp32 && c[q].tile == TILE_SMALL) {
+                const double halo = (double)((c[q].x + 4) * (c[q].y + 4)) / (c[q].x * c[q].y);
+                const double planes = nz + 3.0 * ((nz + zc - 1) / zc);
+                t = std::fmax(t, 4.0 * nx * ny * ((16.0 + has_g) * halo * planes + 9.0 * nz) / 5.1e6);
+            }
             if (t < t_best) {
                 t_best = t;
                 best = FusedPlan{c[q].tile, zc};

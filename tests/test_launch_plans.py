@@ -1,0 +1,40 @@
+"""Rules that choose how a sweep is launched (host code only, no GPU): the
+tile and chunk length of the fused 3D sweep by the grid."""
+import ctypes as C
+import os
+
+import pytest
+
+WIDE, SQUARE, SMALL = 0, 1, 2      # tiles of the fused 3D sweep: 64 x 11, 32 x 16, 16 x 8
+
+
+@pytest.fixture(scope="module")
+def lib():
+    from paper_2305_01701_amd import ep
+    if not os.path.exists(ep.LIB_PATH):
+        from paper_2305_01701_amd import build
+        build.build()
+    return C.CDLL(ep.LIB_PATH)
+
+
+def plan_3d(lib, fp32, with_g, nx, ny, nz):
+    """(tile, planes per chunk) that ep::fused_plan_3d gives for a grid."""
+    f = lib._ZN2ep13fused_plan_3dEbbiiil
+    f.restype = C.c_uint64
+    sy = (nx + 1 + 31) // 32 * 32
+    r = f(C.c_bool(fp32), C.c_bool(with_g), nx, ny, nz, C.c_long(sy * (ny + 1)))
+    return r & 0xffffffff, r >> 32
+
+
+@pytest.mark.parametrize("with_g", [False, True], ids=["uniform", "G"])
+@pytest.mark.parametrize("nz", [3, 4, 6, 8])
+def test_slabs_that_fill_the_chip_take_no_small_tiles(lib, nz, with_g):
+    """500 x 500 FP32 slabs: 2016 small tiles fill the chip and are bound by
+    their halo's bytes (8 planes: 79 us against 63 with 32 x 16 tiles)."""
+    assert plan_3d(lib, True, with_g, 500, 500, nz)[0] == SQUARE
+
+
+def test_small_grids_take_small_tiles(lib):
+    assert plan_3d(lib, True, False, 63, 63, 63) == (SMALL, 4)
+    assert plan_3d(lib, True, False, 300, 300, 5)[0] == SMALL
+    assert plan_3d(lib, False, False, 63, 63, 63) == (SMALL, 4)

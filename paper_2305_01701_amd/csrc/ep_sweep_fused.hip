@@ -58,21 +58,26 @@ struct TileSet {
 constexpr unsigned NOWHERE = 0xffffffffu;
 constexpr int RANGE = 0x7fffffff;
 
-template <typename R>
-__device__ __forceinline__ R buf_load(const char* base, bool go, unsigned off, int plane)
+//
+// Where the planes of a chunk reach beyond 2 GiB (long planes) the plane's
+// offset is added to the base in 64 bits instead.
+template <typename R, typename P>
+__device__ __forceinline__ R buf_load(const char* base, bool go, unsigned off, P plane)
 {
+    if constexpr (sizeof(P) == 8) return buf_load<R>(base + plane, go, off, 0);
     const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, go ? RANGE : 0, 0x00020000);
-    if constexpr (sizeof(R) == 4) return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b32(rs, off, plane, 0));
-    else return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b64(rs, off, plane, 0));
+    if constexpr (sizeof(R) == 4) return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b32(rs, off, (int)plane, 0));
+    else return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b64(rs, off, (int)plane, 0));
 }
 
-template <typename R>
-__device__ __forceinline__ void buf_store(char* base, bool go, unsigned off, int plane, R v)
+template <typename R, typename P>
+__device__ __forceinline__ void buf_store(char* base, bool go, unsigned off, P plane, R v)
 {
+    if constexpr (sizeof(P) == 8) return buf_store<R>(base + plane, go, off, 0, v);
     typedef unsigned u2 __attribute__((ext_vector_type(2)));
     const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, go ? RANGE : 0, 0x00020000);
-    if constexpr (sizeof(R) == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rs, off, plane, 0);
-    else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), rs, off, plane, 0);
+    if constexpr (sizeof(R) == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rs, off, (int)plane, 0);
+    else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), rs, off, (int)plane, 0);
 }
 
 // The value as it is, hidden from the compiler: an expression of it is not
@@ -97,7 +102,7 @@ enum { L_SXY = 0, L_LAM, L_XX, L_YY, L_ZZ, L_NXY, L_NXZ, L_NYZ, L_SINGLE };
 // and faces.  What a stage takes from memory is loaded under the stage's own
 // split one step ahead, right after the previous step's values have been
 // used, into the same registers.
-template <typename R, int TX, int TY, int MODE, int NT, int WPE, bool HG, bool FRZ>
+template <typename R, int TX, int TY, int MODE, int NT, int WPE, bool HG, bool FRZ, bool FAR>
 __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT), amdgpu_waves_per_eu(WPE)))
 void k_fused_3d(SweepArgs<R> a, TileSet ts)
 {
@@ -129,7 +134,9 @@ void k_fused_3d(SweepArgs<R> a, TileSet ts)
 
     // fields: first plane of the chunk of the first field of a group, and the
     // uniform field stride in bytes
-    const int kb = max(k0 - 2, 0), plane_bytes = (int)(a.sz * (long)sizeof(R));
+    using Plane = std::conditional_t<FAR, long, int>;
+    const int kb = max(k0 - 2, 0);
+    const Plane plane_bytes = (Plane)(a.sz * (long)sizeof(R));
     const long first = (long)kb * a.sz;
     const char* const itb = (const char*)(a.it[0] + first);
     char* const nxb = (char*)(a.nx_[0] + first);
@@ -141,7 +148,7 @@ void k_fused_3d(SweepArgs<R> a, TileSet ts)
     long fs = a.fs * (long)sizeof(R);
     // byte offset of plane g in the chunk (planes outside the domain: the
     // nearest; what is read there is not used)
-    auto plane = [&](int g) -> int { return (min(max(g, kb), nz) - kb) * plane_bytes; };
+    auto plane = [&](int g) -> Plane { return (min(max(g, kb), nz) - kb) * plane_bytes; };
     auto off = [&](bool ok, int i, int j) -> unsigned {
         return ok && i >= 0 && i <= nx && j >= 0 && j <= ny ? (unsigned)(i + a.sy * j) * (unsigned)sizeof(R) : NOWHERE;
     };
@@ -176,7 +183,7 @@ void k_fused_3d(SweepArgs<R> a, TileSet ts)
     // velocities of plane (vx, vy) and level (vz) g, and the compliances
     R fvx, fvy, fvz, fig = R(0);
     auto load_v = [&](int g) {
-        const int p = plane(g);
+        const Plane p = plane(g);
         const bool go = g <= k1 + 1;
         fvx = buf_load<R>(itb, go, qo, p);
         fvy = buf_load<R>(itb + fs, go, qo, p);
@@ -204,7 +211,7 @@ void k_fused_3d(SweepArgs<R> a, TileSet ts)
     // centre data of plane c
     R cp, cpo, csx, csxo, csy, csyo, cc;
     auto load_c = [&](int c) {
-        const int p = plane(c);
+        const Plane p = plane(c);
         const bool go = c >= k0 - 1 && c <= k1;
         const char *b = itb + 3 * fs, *o = olb;
         cp = buf_load<R>(b, go, ro, p);
@@ -222,7 +229,7 @@ void k_fused_3d(SweepArgs<R> a, TileSet ts)
     // edge stresses of iteration k of plane and level l
     R kxy, kxz, kyz;
     auto load_k = [&](int l) {
-        const int p = plane(l);
+        const Plane p = plane(l);
         const bool go = l >= k0 && l <= k1;
         const char* b = itb + 6 * fs;
         kxy = buf_load<R>(b, go, eo, p);
@@ -349,7 +356,7 @@ void k_fused_3d(SweepArgs<R> a, TileSet ts)
                 }
             }
             const bool go = c >= k0 && c < k1;
-            const int p = plane(c);
+            const Plane p = plane(c);
             char* b = nxb + 3 * fs;
             buf_store(b, go, ros, p, pn);
             b += fs;
@@ -400,7 +407,7 @@ void k_fused_3d(SweepArgs<R> a, TileSet ts)
                     if (do_l && own_yz) rmax = nmax(rmax, fabs(tyz - kyz) * a.rG);
                 }
             }
-            const int p = plane(l);
+            const Plane p = plane(l);
             char* b = nxb + 6 * fs;
             buf_store(b, do_p, own_xy ? eo : NOWHERE, p, txy);
             b += fs;
@@ -503,7 +510,11 @@ inline void interior_range(int n, int T, int nb, int& b0, int& b1)
     if (b1 < b0) b1 = b0;
 }
 
-template <typename S, typename R, int MODE, bool G = true>
+// Whether a chunk of zc planes of `plane` bytes (with the planes around it)
+// reaches beyond the 32-bit offsets of the buffer accesses.
+inline bool far_planes(int zc, double plane) { return (zc + 8) * plane > 2147483647.0; }
+
+template <typename S, typename R, int MODE, bool G = true, bool LONG = false>
 void run_3d(const SweepArgs<R>& a, hipStream_t s)
 {
     constexpr int TX = S::X, TY = S::Y, NT = S::T, WPE = S::E;
@@ -516,7 +527,14 @@ void run_3d(const SweepArgs<R>& a, hipStream_t s)
     interior_range(a.ny, TY, ts.nby, ts.by0, ts.by1);
     const int nb = ts.nbx * ts.nby * ts.nbz;
     auto go = [&](auto hg, auto frz) {
-        k_fused_3d<R, TX, TY, MODE, NT, WPE, decltype(hg)::value, decltype(frz)::value><<<nb, NT, 0, s>>>(a, ts);
+        constexpr bool HG = decltype(hg)::value, FRZ = decltype(frz)::value;
+        if constexpr (LONG) {
+            if (far_planes(ts.zc, (double)a.sz * sizeof(R))) {
+                k_fused_3d<R, TX, TY, MODE, NT, WPE, HG, FRZ, true><<<nb, NT, 0, s>>>(a, ts);
+                return;
+            }
+        }
+        k_fused_3d<R, TX, TY, MODE, NT, WPE, HG, FRZ, false><<<nb, NT, 0, s>>>(a, ts);
     };
     const bool frz = a.lam_mode == LAM_FROZEN;
     if constexpr (G) {
@@ -533,11 +551,11 @@ void run_3d(const SweepArgs<R>& a, hipStream_t s)
 {
     if constexpr (sizeof(R) == 8) {
         if (a.plan.tile == TILE_SMALL) run_3d<TileD_small, R, MODE>(a, s);
-        else run_3d<TileD_square, R, MODE>(a, s);
+        else run_3d<TileD_square, R, MODE, true, true>(a, s);
     } else {
         if (a.plan.tile == TILE_SMALL) run_3d<TileF_small, R, MODE>(a, s);
         else if (a.plan.tile == TILE_WIDE) run_3d<TileF_wide, R, MODE, false>(a, s);
-        else run_3d<TileF_square, R, MODE>(a, s);
+        else run_3d<TileF_square, R, MODE, true, true>(a, s);
     }
 }
 
@@ -599,10 +617,11 @@ FusedPlan fused_plan_3d(bool fp32, bool has_g, int nx, int ny, int nz, long sz)
         if (has_g && c[q].tile == TILE_WIDE) continue;
         const double columns = (double)((nx + c[q].x - 1) / c[q].x) * ((ny + c[q].y - 1) / c[q].y);
         for (int zc : kChunks) {
-            // the planes of a chunk within the range of 32-bit offsets, the
-            // workgroups within that of a launch
+            // the planes of a chunk within the range of 32-bit offsets (the
+            // 32 x 16 tiles: one plane), the workgroups within that of a launch
             const double nb = columns * ((nz + zc - 1) / zc);
-            if ((zc + 8) * plane > 2147483647.0 || nb * c[q].x * c[q].y > 2147483647.0) continue;
+            if (c[q].tile == TILE_SQUARE ? plane > 2147483647.0 : far_planes(zc, plane)) continue;
+            if (nb * c[q].x * c[q].y > 2147483647.0) continue;
             if (!fp32 && zc > 50 && plane > 1048576.0) continue;
             const double rounds = std::floor(nb / (cus * c[q].res)), rest = nb - rounds * cus * c[q].res;
             double step = rounds * c[q].full * (1.0 + zc / drift);

@@ -38,3 +38,15 @@ def test_small_grids_take_small_tiles(lib):
     assert plan_3d(lib, True, False, 63, 63, 63) == (SMALL, 4)
     assert plan_3d(lib, True, False, 300, 300, 5)[0] == SMALL
     assert plan_3d(lib, False, False, 63, 63, 63) == (SMALL, 4)
+
+
+@pytest.mark.parametrize("fp32,grid", [(False, (4959, 4950, 3)), (False, (4959, 4950, 8)), (True, (7200, 7100, 5))])
+def test_long_planes_keep_the_fused_sweep(lib, fp32, grid):
+    """Planes of which no chunk fits into 2 GiB (FP64 4959 x 4950: 196 MB)
+    run in the fused sweep, on its 32 x 16 tiles."""
+    tile, zc = plan_3d(lib, fp32, False, *grid)
+    assert tile == SQUARE and zc >= 3
+
+
+def test_planes_beyond_2_gib_are_out_of_range(lib):
+    assert plan_3d(lib, False, False, 20000, 20000, 3)[1] == 0

@@ -258,18 +258,21 @@ void k_fused_3d(SweepArgs<R> a, TileSet ts)
     R mxz = R(0), myz = R(0), uxz = R(0), uyz = R(0), uzz = R(0), ux = R(0), uy = R(0);
     R txy = R(0), txz = R(0), tyz = R(0);      // new edge stresses of this step
 
-    load_v(k0 - 2);
-    stage_v(k0 & 1);
-    load_v(k0 - 1);
-    stage_v((k0 & 1) ^ 1);
-    load_old(k0 - 1);
-    load_c(k0 - 2);
-    load_k(k0 - 2);
-    load_w(k0 - 3);
-    load_v(k0);
+    // nothing below plane 0 is used, so its chunk starts a step later (slabs of
+    // 3 planes: 5 steps instead of 6)
+    const int f0 = max(k0 - 1, 0);
+    load_v(f0 - 1);
+    stage_v((f0 & 1) ^ 1);
+    load_v(f0);
+    stage_v(f0 & 1);
+    load_old(f0);
+    load_c(f0 - 1);
+    load_k(f0 - 1);
+    load_w(f0 - 2);
+    load_v(f0 + 1);
     __syncthreads();
     // f - 1 is the plane of the centres, f - 2 that of the vx and vy updates
-    for (int f = k0 - 1; f <= k1 + 1; ++f) {
+    for (int f = f0; f <= k1 + 1; ++f) {
         asm volatile("" : "+s"(fs));
         const int sc = f & 1;                 // slot of plane f; plane f - 1 has the other one
         R* const sf = s0 + sc * SL;

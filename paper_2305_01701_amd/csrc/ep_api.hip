@@ -272,18 +272,17 @@ SweepArgs<float> args32(const ep_handle* h, int from)
     return make_args<float>(h, h->it32[from], h->it32[1 - from], h->old32, h->coh32, h->lam32, false);
 }
 
-// Launch of ns sweeps of a 2D model with its own tile shape.
+// Launch of ns sweeps of a 2D model with its own tile shapes.
 Launch2d launch_2d(const ep_handle* h, bool fp32, int mode, int ns)
 {
     Launch2d l;
-    l.shape = h->shape2[fp32];
+    l.shape = h->shape2[fp32][ns == 1];
     l.mode = mode;
     l.ns = ns;
-    const int tx = mode == MODE_PHYS ? PHYS_TILE : kTiles2d[fp32][l.shape].tx;
-    const int ty = mode == MODE_PHYS ? PHYS_TILE : kTiles2d[fp32][l.shape].ty;
+    const int tx = kTiles2d[fp32][l.shape].tx, ty = kTiles2d[fp32][l.shape].ty;
     l.nbx = (h->nx + tx - 1) / tx;
     l.tiles = (int)std::min<long>((long)l.nbx * ((h->ny + ty - 1) / ty), INT_MAX);
-    l.grid = std::min(l.tiles, h->grid2[fp32]);
+    l.grid = ns == 1 ? l.tiles : std::min(l.tiles, h->grid2[fp32]);     // one tile each, or a persistent grid
     l.has_g = h->has_g;
     return l;
 }
@@ -292,7 +291,7 @@ Launch2d launch_2d(const ep_handle* h, bool fp32, int mode, int ns)
 int sweeps_per_launch(const ep_handle* h, bool fp32)
 {
     const bool fused = fp32 ? h->fused32 : h->fused64;
-    return h->ndim == 2 && fused ? kTiles2d[fp32][h->shape2[fp32]].k : 1;
+    return h->ndim == 2 && fused ? kTiles2d[fp32][h->shape2[fp32][0]].k : 1;
 }
 
 // ns PT sweeps reading buffer `from` (physical: pseudo-time terms removed;
@@ -913,7 +912,8 @@ int handle_create(const ep_params* p, const double* cohesion, char* d_workspace,
         int ncu = 0;
         if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, 0) != hipSuccess || ncu <= 0) ncu = 256;
         for (int q = 0; q < 2; ++q) {
-            const int sh = h->shape2[q] = tile2d_choice(q == 1, h->nx, h->ny, ncu);
+            const int sh = h->shape2[q][0] = tile2d_choice(q == 1, h->nx, h->ny, ncu);
+            h->shape2[q][1] = tile2d_one_sweep(q == 1, h->nx, h->ny, ncu);
             h->grid2[q] = ncu * std::min(8, q ? batch_blocks_per_cu<float>(sh) : batch_blocks_per_cu<double>(sh));
         }
         if (upload_tables(h) != EP_OK) return fail(EP_EDEVICE);

@@ -62,11 +62,11 @@ struct ep_handle {
     long t_n[2];
     std::vector<double> hist_r;
     std::vector<int> hist_p;
-    // 2D: argument tables of the tile kernel, [FP64, FP32] tile shape and
-    // resident workgroups of this model
+    // 2D: argument tables of the tile kernel; tile shapes of this model, [FP64,
+    // FP32][several sweeps, one sweep a launch], and resident workgroups
     ep::SweepArgs<double>* tab64;
     ep::SweepArgs<float>* tab32;
-    int shape2[2], grid2[2];
+    int shape2[2][2], grid2[2];
     ep::StepCtl ctl;
     double* compact64;     // a field without padding, on its way to or from the host
     double* vguess64[3];   // 3D: velocities of a supplied starting guess

@@ -96,8 +96,8 @@ struct Tile2d {
     int pass_x, pass_y;    // points one pass of its threads covers (the shape's name)
     double t1, t0, t2;     // cost of a launch (tile2d_cost)
 };
-extern const Tile2d kTiles2d[2][BATCH_SHAPES];   // [FP64, FP32]
-constexpr int PHYS_TILE = 24;                     // side of the tiles of physical evaluations
+constexpr int ONE_SWEEP = BATCH_SHAPES;           // two more for launches of one sweep: 60 x 12 cells, 60 x 28
+extern const Tile2d kTiles2d[2][BATCH_SHAPES + 2];   // [FP64, FP32]
 inline long tiles2d(bool fp32, int shape, int nx, int ny)
 {
     const Tile2d& t = kTiles2d[fp32][shape];
@@ -107,9 +107,11 @@ inline long tiles2d(bool fp32, int shape, int nx, int ny)
 // of least modelled time for one model.
 double tile2d_cost(bool fp32, int shape, long tiles, int cus);
 int tile2d_choice(bool fp32, int nx, int ny, int cus);
+// Shape of a launch of one sweep of one model.
+int tile2d_one_sweep(bool fp32, int nx, int ny, int cus);
 
 struct Launch2d {
-    int shape, mode, ns;   // ns <= K sweeps; the last one reduces when mode is MODE_CHECK
+    int shape, mode, ns;   // ns <= K sweeps (MODE_PHYS: a shape of one sweep); the last one reduces when mode is MODE_CHECK
     int grid;              // workgroups (they walk the tiles)
     int tiles, nbx;        // tiles of the model and per row of it (without a list)
     bool has_g;            // per-cell shear modulus (single models)

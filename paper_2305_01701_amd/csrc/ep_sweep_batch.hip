@@ -44,18 +44,28 @@ void k_batch_2d(const SweepArgs<R>* __restrict__ table, const TileRef* __restric
 // Tile shapes of each precision: index, TX, TY, K, threads, waves per SIMD to
 // fit in registers.  The first six are the tuner's, named by the points that
 // one pass of the workgroup's threads covers (64 x 8, 64 x 4, 32 x 8, 128 x 4,
-// 64 x 16, 32 x 16).
+// 64 x 16, 32 x 16), the last two those of launches of one sweep.
 #define EP_TILES_32(X) X(0, 52, 20, 3, 512, 6) X(1, 56, 8, 2, 256, 5) X(2, 24, 24, 2, 256, 5) X(3, 120, 8, 2, 512, 5) \
     X(4, 52, 20, 3, 1024, 8) X(5, 24, 24, 2, 512, 8) X(6, 12, 12, 5, 1024, 8) X(7, 16, 16, 4, 1024, 8)              \
-    X(8, 20, 20, 3, 1024, 8) X(9, 32, 32, 4, 768, 6)
+    X(8, 20, 20, 3, 1024, 8) X(9, 32, 32, 4, 768, 6) X(10, 60, 12, 1, 512, 6) X(11, 60, 28, 1, 1024, 8)
 #define EP_TILES_64(X) X(0, 56, 8, 2, 512, 4) X(1, 56, 8, 2, 256, 3) X(2, 24, 24, 2, 256, 3) X(3, 120, 8, 2, 512, 2) \
     X(4, 52, 20, 3, 1024, 4) X(5, 24, 24, 2, 512, 4) X(6, 12, 12, 5, 1024, 4) X(7, 16, 16, 4, 1024, 4)              \
-    X(8, 20, 20, 3, 1024, 4) X(9, 20, 20, 3, 512, 4)
+    X(8, 20, 20, 3, 1024, 4) X(9, 20, 20, 3, 512, 4) X(10, 60, 12, 1, 512, 4) X(11, 60, 28, 1, 1024, 4)
 
 template <typename R, int TX, int TY, int K, int NT, int E>
 void run(const SweepArgs<R>* table, const TileRef* list, const int* count, const Launch2d& l, hipStream_t s)
 {
     const int grid = l.grid > 0 ? l.grid : 1;
+    if constexpr (K == 1 && sizeof(R) == 8) {
+        if (l.mode == MODE_PHYS) {
+            // physical evaluations: single FP64 models
+            if (l.has_g)
+                k_batch_2d<R, TX, TY, K, MODE_PHYS, NT, E, true><<<grid, NT, 0, s>>>(table, list, count, l.tiles, l.nbx, 1);
+            else
+                k_batch_2d<R, TX, TY, K, MODE_PHYS, NT, E, false><<<grid, NT, 0, s>>>(table, list, count, l.tiles, l.nbx, 1);
+            return;
+        }
+    }
     if (l.has_g) {
         if (l.mode == MODE_CHECK)
             k_batch_2d<R, TX, TY, K, MODE_CHECK, NT, E, true><<<grid, NT, 0, s>>>(table, list, count, l.tiles, l.nbx, l.ns);
@@ -81,16 +91,16 @@ int occupancy()
 
 // What a launch with a shape costs, in us: alone with at most one workgroup
 // per CU (t1), else t0 + t2 per workgroup on a CU; measured on 18 grids from
-// 31^2 to 2047^2.
-const Tile2d kTiles2d[2][BATCH_SHAPES] = {
+// 31^2 to 2047^2 (not of the shapes of one sweep: tile2d_one_sweep).
+const Tile2d kTiles2d[2][BATCH_SHAPES + 2] = {
     {{56, 8, 2, 64, 8, 10.5, 4.5, 5.7}, {56, 8, 2, 64, 4, 13.0, 7.0, 5.6}, {24, 24, 2, 32, 8, 15.0, 8.0, 6.0},
      {120, 8, 2, 128, 4, 16.0, 3.0, 13.0}, {52, 20, 3, 64, 16, 20.5, 1.0, 20.5}, {24, 24, 2, 32, 16, 11.0, 4.5, 6.2},
      {12, 12, 5, 32, 32, 15.8, 1.8, 14.0}, {16, 16, 4, 32, 32, 14.0, 2.0, 12.3}, {20, 20, 3, 32, 32, 12.0, 1.5, 10.7},
-     {20, 20, 3, 32, 16, 13.7, 5.0, 7.6}},
+     {20, 20, 3, 32, 16, 13.7, 5.0, 7.6}, {60, 12, 1, 64, 8, 0, 0, 0}, {60, 28, 1, 64, 16, 0, 0, 0}},
     {{52, 20, 3, 64, 8, 15.7, 5.0, 7.0}, {56, 8, 2, 64, 4, 10.0, 2.0, 2.6}, {24, 24, 2, 32, 8, 10.0, 2.0, 3.5},
      {120, 8, 2, 128, 4, 11.0, 2.0, 6.4}, {52, 20, 3, 64, 16, 11.2, 3.0, 6.9}, {24, 24, 2, 32, 16, 8.0, 1.5, 3.2},
      {12, 12, 5, 32, 32, 9.6, 1.7, 5.9}, {16, 16, 4, 32, 32, 8.5, 1.6, 4.9}, {20, 20, 3, 32, 32, 7.4, 2.3, 3.9},
-     {32, 32, 4, 48, 16, 17.0, 2.5, 10.2}}};
+     {32, 32, 4, 48, 16, 17.0, 2.5, 10.2}, {60, 12, 1, 64, 8, 0, 0, 0}, {60, 28, 1, 64, 16, 0, 0, 0}}};
 
 double tile2d_cost(bool fp32, int shape, long tiles, int cus)
 {
@@ -119,18 +129,28 @@ int tile2d_choice(bool fp32, int nx, int ny, int cus)
     return best;
 }
 
+// A launch of one sweep has no use for the wide halo of the shapes above
+// (1023^2 FP32: 47 us by events where 60 x 28 tiles take 38; 2047^2 FP64 with a
+// per-cell G 344 and 208): tiles with a halo of two points.  60 x 12 (512
+// threads) unless 60 x 28 (1024) spare the CUs a second workgroup (511^2 FP64
+// 27.5 us, 60 x 12 32.5), or in FP32, where two and three of them fit a CU at a
+// time, rounds: 17 us one of 60 x 28, 12 us one of 60 x 12 (1500^2: 62 and 75
+// us; 2047^2: 132 and 111).  In FP64 the larger tiles never gain there (1023^2:
+// 66 and 62.5 us).
+int tile2d_one_sweep(bool fp32, int nx, int ny, int cus)
+{
+    const long t12 = tiles2d(fp32, ONE_SWEEP, nx, ny), t28 = tiles2d(fp32, ONE_SWEEP + 1, nx, ny);
+    auto rounds = [&](long tiles, long per_cu) { return (tiles + per_cu * cus - 1) / (per_cu * cus); };
+    const bool large = (t28 <= cus && t12 > cus) || (fp32 && 17 * rounds(t28, 2) < 12 * rounds(t12, 3));
+    return ONE_SWEEP + large;
+}
+
 template <typename R>
 void launch_sweep_batch_2d(const SweepArgs<R>* table, const TileRef* list, const int* count, const Launch2d& l,
                            hipStream_t s)
 {
 #define X(i, TX, TY, K, NT, E) case i: run<R, TX, TY, K, NT, E>(table, list, count, l, s); break;
     if constexpr (sizeof(R) == 8) {
-        if (l.mode == MODE_PHYS) {
-            // physical evaluations: single FP64 models, once or twice an increment
-            if (l.has_g) k_batch_2d<R, 24, 24, 2, MODE_PHYS, 512, 4, true><<<l.grid, 512, 0, s>>>(table, list, count, l.tiles, l.nbx, 1);
-            else k_batch_2d<R, 24, 24, 2, MODE_PHYS, 512, 4, false><<<l.grid, 512, 0, s>>>(table, list, count, l.tiles, l.nbx, 1);
-            return;
-        }
         switch (l.shape) { EP_TILES_64(X) }
     } else {
         switch (l.shape) { EP_TILES_32(X) }

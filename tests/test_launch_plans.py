@@ -50,3 +50,18 @@ def test_long_planes_keep_the_fused_sweep(lib, fp32, grid):
 
 def test_planes_beyond_2_gib_are_out_of_range(lib):
     assert plan_3d(lib, False, False, 20000, 20000, 3)[1] == 0
+
+
+def one_sweep(lib, fp32, nx, ny):
+    f = lib._ZN2ep16tile2d_one_sweepEbiii
+    f.restype = C.c_int
+    return f(C.c_bool(fp32), nx, ny, 256)
+
+
+def test_single_2d_sweeps_take_tiles_without_a_wide_halo(lib):
+    """One sweep per launch: 60 x 12 tiles (10), 60 x 28 (11) where they spare
+    the CUs a second workgroup or, in FP32, rounds of workgroups."""
+    for fp32 in (False, True):
+        assert one_sweep(lib, fp32, 63, 63) == 10 and one_sweep(lib, fp32, 700, 700) == 10
+        assert one_sweep(lib, fp32, 511, 511) == 11 and one_sweep(lib, fp32, 2047, 2047) == 10
+    assert one_sweep(lib, True, 1023, 1023) == 11 and one_sweep(lib, False, 1023, 1023) == 10

@@ -109,7 +109,6 @@ size_t carve(const ep_params* p, ep_handle* h, char* base)
     q = take(b64); if (h) h->lamdot64 = (double*)q;
     q = take(b64); if (h) h->tii64 = (double*)q;
     q = take(b64); if (h) h->yld64 = (double*)q;
-    q = take(b64); if (h) h->compact64 = (double*)q;
     q = take(4 * sizeof(double)); if (h) h->cols64 = (double*)q;
     q = take(RED_N * sizeof(unsigned long long)); if (h) h->red = (unsigned long long*)q;
     for (int b = 0; b < 2; ++b)
@@ -133,6 +132,7 @@ size_t carve(const ep_params* p, ep_handle* h, char* base)
         q = take(6 * sizeof(SweepArgs<float>)); if (h) h->tab32 = (SweepArgs<float>*)q;
     }
     if (h) {
+        h->compact64 = h->vstart64[0];
         h->sy = (int)sy;
         h->sz = sz;
         h->nelem = nelem;

@@ -68,7 +68,8 @@ struct ep_handle {
     ep::SweepArgs<float>* tab32;
     int shape2[2][2], grid2[2];
     ep::StepCtl ctl;
-    double* compact64;     // a field without padding, on its way to or from the host
+    double* compact64;     // a field without padding, on its way to or from the host (vstart64[0], which
+                           // every increment writes first and nothing reads after it)
     double* vguess64[3];   // 3D: velocities of a supplied starting guess
     bool guess_ready;      // the next increment tries vguess64
     int freeze;            // 0 off, 1 the next sweep stores Lambda, 2 Lambda frozen

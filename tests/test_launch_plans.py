@@ -65,3 +65,18 @@ def test_single_2d_sweeps_take_tiles_without_a_wide_halo(lib):
         assert one_sweep(lib, fp32, 63, 63) == 10 and one_sweep(lib, fp32, 700, 700) == 10
         assert one_sweep(lib, fp32, 511, 511) == 11 and one_sweep(lib, fp32, 2047, 2047) == 10
     assert one_sweep(lib, True, 1023, 1023) == 11 and one_sweep(lib, False, 1023, 1023) == 10
+
+
+@pytest.mark.parametrize("fp32", [False, True], ids=["fp64", "fp32"])
+def test_workspace_holds_no_field_for_transfers(lib, fp32):
+    """3D: 46 FP64 fields (two sets of 9 iterates, 6 increment-start ones,
+    cohesion, Lambda, compliance, start velocities, displacements, strains, 4
+    diagnostics, guess), with FP32 iterates 27 more in FP32; the array that
+    packs a field for the host is one of them."""
+    from ep_workloads import c3_3d
+    from paper_2305_01701_amd import ep
+    m = c3_3d()
+    nelem = (m.nx + 1 + 31) // 32 * 32 * (m.ny + 1) * (m.nz + 1)
+    fields = 46 * 8 + (27 * 4 if fp32 else 0)
+    ws = ep.ep_workspace_size(ep.params_from_model(m, precision=ep.EP_FP32_FIELDS if fp32 else ep.EP_FP64))
+    assert fields * nelem <= ws <= fields * nelem + 75 * 256 + 4096

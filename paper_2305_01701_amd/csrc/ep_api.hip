@@ -10,6 +10,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <vector>
 
@@ -833,8 +834,23 @@ int move_rows(ep_handle* h, double* a, const double* b, const int ext[3])
     return EP_OK;
 }
 
+constexpr long SMALL_FIELD = 40000;          // elements, padding included
+
 int download(ep_handle* h, double* a, const double* b, double* out, const int ext[3])
 {
+    // small fields: the padded array at once and its rows on the host, without
+    // a launch before the copy (63^2: 17 against 28 us per field, 31^3: 32
+    // against 41; 511^2: 230 against 155)
+    std::unique_ptr<double[]> pad;
+    if (!b && h->nelem <= SMALL_FIELD) pad.reset(new (std::nothrow) double[h->nelem]);
+    if (pad) {
+        HIPCHK(h, hipMemcpyAsync(pad.get(), a, h->nelem * sizeof(double), hipMemcpyDeviceToHost, h->st));
+        HIPCHK(h, hipStreamSynchronize(h->st));
+        for (int k = 0; k < ext[2]; ++k)
+            for (int j = 0; j < ext[1]; ++j, out += ext[0])
+                std::memcpy(out, pad.get() + (long)h->sy * j + h->sz * k, ext[0] * sizeof(double));
+        return EP_OK;
+    }
     int rc = move_rows<true>(h, a, b, ext);
     if (rc) return rc;
     HIPCHK(h, hipMemcpyAsync(out, h->compact64, (size_t)ext[0] * ext[1] * ext[2] * sizeof(double), hipMemcpyDeviceToHost,

@@ -374,8 +374,8 @@ int ep_batch_init(int n, const ep_params* p, const double* const* cohesion, void
                   void* stream, ep_batch** out);
 
 /* Autotuner: picks the tile shape of each model size (models with equal
- * nx, ny share one) by timing 6 * `reps` batched sweeps of all models per
- * candidate, coordinate descent over the size classes; FP32-field batches
+ * nx, ny share one) by timing `reps` batched sweeps of all models (rounded up
+ * to a multiple of 6: whole launches) per candidate, coordinate descent over the size classes; FP32-field batches
  * get a second shape per size for their FP64 finishing sweeps, tuned the
  * same way.  The timed sweeps leave the state unchanged.  Optional; the
  * default shape is 64 x 8. */

@@ -323,6 +323,8 @@ void destroy_batch(ep_batch* b)
 
 }  // namespace
 
+int ep::tuned_sweeps(int reps) { return (int)std::min((reps + 5L) / 6 * 6, 2147483646L); }
+
 // =========================================================================
 extern "C" {
 
@@ -430,16 +432,16 @@ int ep_batch_tune(ep_batch* b, int reps)
             int rc = upload(b);
             if (rc) return rc;
             const unsigned mask = list_mask(b);
-            // whole launches of the shapes with two and with three sweeps
-            enqueue_sweeps(b, 6, false, false, false, mask, b->st);    // warm-up
+            const int n = tuned_sweeps(reps);
+            enqueue_sweeps(b, 1, false, false, false, mask, b->st);    // warm-up
             BCHK(b, hipEventRecord(b->ev0, b->st));
-            enqueue_sweeps(b, 6 * reps, false, false, false, mask, b->st);
+            enqueue_sweeps(b, n, false, false, false, mask, b->st);
             BCHK(b, hipEventRecord(b->ev1, b->st));
             BCHK(b, hipEventSynchronize(b->ev1));
             BCHK(b, hipGetLastError());
             float t = 0.f;
             BCHK(b, hipEventElapsedTime(&t, b->ev0, b->ev1));
-            *ms = t / reps;
+            *ms = t / n;
             return EP_OK;
         };
         double best = 0;

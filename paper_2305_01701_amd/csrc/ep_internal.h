@@ -96,6 +96,9 @@ struct Tile2d {
     int pass_x, pass_y;    // points one pass of its threads covers (the shape's name)
     double t1, t0, t2;     // cost of a launch (tile2d_cost)
 };
+// Sweeps that the autotuner times for `reps` requested ones: whole launches of
+// the shapes with two and with three sweeps.
+int tuned_sweeps(int reps);
 constexpr int ONE_SWEEP = BATCH_SHAPES;           // two more for launches of one sweep: 60 x 12 cells, 60 x 28
 extern const Tile2d kTiles2d[2][BATCH_SHAPES + 2];   // [FP64, FP32]
 inline long tiles2d(bool fp32, int shape, int nx, int ny)

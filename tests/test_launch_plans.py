@@ -80,3 +80,9 @@ def test_workspace_holds_no_field_for_transfers(lib, fp32):
     fields = 46 * 8 + (27 * 4 if fp32 else 0)
     ws = ep.ep_workspace_size(ep.params_from_model(m, precision=ep.EP_FP32_FIELDS if fp32 else ep.EP_FP64))
     assert fields * nelem <= ws <= fields * nelem + 75 * 256 + 4096
+
+
+@pytest.mark.parametrize("reps,sweeps", [(1, 6), (3, 6), (5, 6), (6, 6), (7, 12), (100, 102), (2 ** 31 - 1, 2 ** 31 - 2)])
+def test_the_tuner_times_the_sweeps_it_is_asked_for(lib, reps, sweeps):
+    """Rounded up to whole launches of shapes with two and with three sweeps."""
+    assert lib._ZN2ep12tuned_sweepsEi(reps) == sweeps

@@ -377,7 +377,9 @@ int ep_batch_init(int n, const ep_params* p, const double* const* cohesion, void
  * nx, ny share one) by timing `reps` batched sweeps of all models (rounded up
  * to a multiple of 6: whole launches) per candidate, coordinate descent over the size classes; FP32-field batches
  * get a second shape per size for their FP64 finishing sweeps, tuned the
- * same way.  The timed sweeps leave the state unchanged.  Optional; the
+ * same way.  While few models are left, the batch still uses shapes for few
+ * tiles, where the tuner's times of those, scaled to what is left, are
+ * shorter.  The timed sweeps leave the state unchanged.  Optional; the
  * default shape is 64 x 8. */
 int ep_batch_tune(ep_batch* b, int reps);
 

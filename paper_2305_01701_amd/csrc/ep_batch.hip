@@ -41,6 +41,7 @@ struct ep_batch {
     std::vector<int> shape;             // tile shape per model (sweeps in the batch precision)
     std::vector<int> shape64;           // FP32-field batches: tile shape of the FP64 finishing sweeps
     int ncu;
+    double scale[2][BATCH_SHAPES], own_scale[2];   // [FP64, FP32] tuner's times over the modelled (1: not tuned)
     unsigned long long* red;            // n x RED_N
     double* cols;                       // n x 4
     SweepArgs<double>* tab64;           // 2 x n (parity of the ping-pong buffers)
@@ -156,11 +157,27 @@ void fill_tables(ep_batch* b)
     }
 }
 
+int own_shape(const ep_batch* b, int i, int q) { return (q == 1 || !b->fp32) ? b->shape[i] : b->shape64[i]; }
+
+// Tiles of the models that are active in precision q, with their own shapes
+// and with each shape for all of them.
+template <typename F>
+void count_tiles(const ep_batch* b, int q, F active, long* own, long* tiles)
+{
+    std::fill(own, own + BATCH_SHAPES, 0L);
+    std::fill(tiles, tiles + BATCH_SHAPES, 0L);
+    for (int i = 0; i < b->n; ++i) {
+        if (!active(i, q)) continue;
+        const ep_handle* h = b->m[i];
+        own[own_shape(b, i, q)] += tiles2d(q == 1, own_shape(b, i, q), h->nx, h->ny);
+        for (int s = 0; s < BATCH_SHAPES; ++s) tiles[s] += tiles2d(q == 1, s, h->nx, h->ny);
+    }
+}
+
 // Tile lists of the running models (precision of each model's current
 // sweeps), or of all models when all_models is set, in FP32 when all32 (the
 // batch precision) else in FP64.  Running models of a precision take their
-// (tuned) shapes, or together one of the others where the launch then has
-// less modelled time: the shapes for few tiles once few models are left.
+// (tuned) shapes, or together one of the others (tile2d_common).
 void fill_lists(ep_batch* b, bool all_models, bool all32 = true)
 {
     for (int q = 0; q < 2; ++q)
@@ -170,31 +187,17 @@ void fill_lists(ep_batch* b, bool all_models, bool all32 = true)
         if (all_models) return (b->fp32 && all32) == (q == 1);
         return b->m[i]->ctl.running && b->m[i]->ctl.use32 == (q == 1);
     };
-    auto own_shape = [&](int i, int q) { return (q == 1 || !b->fp32) ? b->shape[i] : b->shape64[i]; };
     for (int q = 0; q < 2; ++q) {
         int common = -1;
         if (!all_models) {
-            long own[BATCH_SHAPES] = {};
-            double t_own = 0;
-            for (int i = 0; i < b->n; ++i)
-                if (active(i, q)) own[own_shape(i, q)] += tiles2d(q == 1, own_shape(i, q), b->m[i]->nx, b->m[i]->ny);
-            for (int s = 0; s < BATCH_SHAPES; ++s)
-                if (own[s] > 0) t_own += tile2d_cost(q == 1, s, own[s], b->ncu);
-            for (int s = TUNED_SHAPES; s < BATCH_SHAPES; ++s) {
-                long tiles = 0;
-                for (int i = 0; i < b->n; ++i)
-                    if (active(i, q)) tiles += tiles2d(q == 1, s, b->m[i]->nx, b->m[i]->ny);
-                const double t = tile2d_cost(q == 1, s, tiles, b->ncu);
-                if (tiles > 0 && t < t_own) {
-                    t_own = t;
-                    common = s;
-                }
-            }
+            long own[BATCH_SHAPES], tiles[BATCH_SHAPES];
+            count_tiles(b, q, active, own, tiles);
+            common = tile2d_common(q == 1, own, tiles, b->scale[q], b->own_scale[q], b->ncu);
         }
         for (int i = 0; i < b->n; ++i) {
             if (!active(i, q)) continue;
             ep_handle* h = b->m[i];
-            const int s = common >= 0 ? common : own_shape(i, q);
+            const int s = common >= 0 ? common : own_shape(b, i, q);
             const int tx = kTiles2d[q][s].tx, ty = kTiles2d[q][s].ty;
             const int nbx = (h->nx + tx - 1) / tx, nby = (h->ny + ty - 1) / ty;
             auto& L = b->h_list[q][s];
@@ -323,6 +326,17 @@ void destroy_batch(ep_batch* b)
 
 }  // namespace
 
+// All models' sweeps with one shape (for tests, which so reach every one).
+int ep::batch_use_shape(ep_batch* b, int shape)
+{
+    if (!b || shape < 0 || shape >= BATCH_SHAPES) return EP_EINVAL;
+    std::fill(b->shape.begin(), b->shape.end(), shape);
+    std::fill(b->shape64.begin(), b->shape64.end(), shape);
+    b->own_scale[0] = b->own_scale[1] = 0.0;
+    drop_graphs(b);
+    return EP_OK;
+}
+
 int ep::tuned_sweeps(int reps) { return (int)std::min((reps + 5L) / 6 * 6, 2147483646L); }
 
 // =========================================================================
@@ -378,6 +392,10 @@ int ep_batch_init(int n, const ep_params* p, const double* const* cohesion, void
     int ncu = 0;
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, 0) != hipSuccess || ncu <= 0) ncu = 256;
     b->ncu = ncu;
+    for (int q = 0; q < 2; ++q) {
+        std::fill(b->scale[q], b->scale[q] + BATCH_SHAPES, 1.0);
+        b->own_scale[q] = 1.0;
+    }
     for (int s = 0; s < BATCH_SHAPES; ++s) {
         b->grid[0][s] = ncu * std::min(8, batch_blocks_per_cu<double>(s));
         b->grid[1][s] = ncu * std::min(8, batch_blocks_per_cu<float>(s));
@@ -447,7 +465,8 @@ int ep_batch_tune(ep_batch* b, int reps)
         double best = 0;
         int rc = time_config(&best);
         if (rc) return rc;
-        for (int pass = 0; pass < 2; ++pass) {
+        // (one size class: a second pass would time the same again)
+        for (int pass = 0; pass < (classes.size() > 1 ? 2 : 1); ++pass) {
             for (auto& cl : classes) {
                 const int keep = shape[cl.second[0]];
                 int best_s = keep;
@@ -464,7 +483,24 @@ int ep_batch_tune(ep_batch* b, int reps)
                 for (int i : cl.second) shape[i] = best_s;
             }
         }
-        return EP_OK;
+        // the tuned shapes and those for few tiles against their modelled times
+        const int q = b->fp32 && all32 ? 1 : 0;
+        const auto all = [](int, int) { return true; };
+        long own[BATCH_SHAPES], tiles[BATCH_SHAPES];
+        count_tiles(b, q, all, own, tiles);
+        double model = 0;
+        for (int s = 0; s < BATCH_SHAPES; ++s)
+            if (own[s] > 0) model += tile2d_cost(q == 1, s, own[s], b->ncu);
+        b->own_scale[q] = best * 1e3 / model;
+        const std::vector<int> tuned = shape;
+        for (int s = TUNED_SHAPES; s < BATCH_SHAPES && rc == EP_OK; ++s) {
+            std::fill(shape.begin(), shape.end(), s);
+            double t = 0;
+            rc = time_config(&t);
+            b->scale[q][s] = t * 1e3 / tile2d_cost(q == 1, s, tiles[s], b->ncu);
+        }
+        shape = tuned;
+        return rc;
     };
     int rc = descend(b->shape, true);
     if (rc) return rc;

@@ -129,6 +129,7 @@ bool step_certify(ep_handle* h, const double red[RED_N]);
 void check_limits(ep_handle* h);
 int step_finish(ep_handle* h);
 void step_report(ep_handle* h, const double red[RED_N], const double cols[4]);
+int batch_use_shape(ep_batch* b, int shape);
 // Reduction slots as doubles (raw uint64 patterns; RED_NYIELD is a count).
 void decode_red(const unsigned long long raw[RED_N], double out[RED_N]);
 

@@ -110,6 +110,10 @@ inline long tiles2d(bool fp32, int shape, int nx, int ny)
 // of least modelled time for one model.
 double tile2d_cost(bool fp32, int shape, long tiles, int cus);
 int tile2d_choice(bool fp32, int nx, int ny, int cus);
+// The shape behind the tuned ones that all running models of a batch take
+// together (tiles[s] tiles with shape s), or -1: their own (own[s] tiles).
+// scale: measured over modelled time of each shape, own_scale: of their own.
+int tile2d_common(bool fp32, const long* own, const long* tiles, const double* scale, double own_scale, int cus);
 // Shape of a launch of one sweep of one model.
 int tile2d_one_sweep(bool fp32, int nx, int ny, int cus);
 

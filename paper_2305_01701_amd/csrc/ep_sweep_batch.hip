@@ -129,6 +129,27 @@ int tile2d_choice(bool fp32, int nx, int ny, int cus)
     return best;
 }
 
+// Where few models of a batch are left, the shapes for few tiles take less
+// time.  Once the tuner has run, both sides are scaled by what it measured
+// with all models, so that a shape it chose gives way only to one that its
+// own times favour.
+int tile2d_common(bool fp32, const long* own, const long* tiles, const double* scale, double own_scale, int cus)
+{
+    double best = 0;
+    for (int s = 0; s < BATCH_SHAPES; ++s)
+        if (own[s] > 0) best += tile2d_cost(fp32, s, own[s], cus);
+    best *= own_scale;
+    int common = -1;
+    for (int s = TUNED_SHAPES; s < BATCH_SHAPES; ++s) {
+        const double t = scale[s] * tile2d_cost(fp32, s, tiles[s], cus);
+        if (tiles[s] > 0 && t < best) {
+            best = t;
+            common = s;
+        }
+    }
+    return common;
+}
+
 // A launch of one sweep has no use for the wide halo of the shapes above
 // (1023^2 FP32: 47 us by events where 60 x 28 tiles take 38; 2047^2 FP64 with a
 // per-cell G 344 and 208): tiles with a halo of two points.  60 x 12 (512

@@ -86,3 +86,27 @@ def test_workspace_holds_no_field_for_transfers(lib, fp32):
 def test_the_tuner_times_the_sweeps_it_is_asked_for(lib, reps, sweeps):
     """Rounded up to whole launches of shapes with two and with three sweeps."""
     assert lib._ZN2ep12tuned_sweepsEi(reps) == sweeps
+
+
+def common_shape(lib, fp32, own, tiles, scale=None, own_scale=1.0):
+    f = lib._ZN2ep13tile2d_commonEbPKlS1_PKddi
+    f.restype = C.c_int
+    arr = lambda d: (C.c_long * 10)(*[d.get(s, 0) for s in range(10)])
+    sc = (C.c_double * 10)(*[(scale or {}).get(s, 1.0) for s in range(10)])
+    return f(C.c_bool(fp32), arr(own), arr(tiles), sc, C.c_double(own_scale), 256)
+
+
+@pytest.mark.parametrize("fp32", [False, True], ids=["fp64", "fp32"])
+def test_tuned_shapes_give_way_only_to_the_tuners_own_times(lib, fp32):
+    """Three models of 63 x 63 cells: the shapes for few tiles are modelled faster
+    than shape 0; where the tuner measured them slower than the shapes it chose,
+    these stay, and where it measured 16 x 16 tiles (7) as the fastest, all
+    models take those."""
+    cells = {0: (52, 20) if fp32 else (56, 8), 6: (12, 12), 7: (16, 16), 8: (20, 20), 9: (32, 32) if fp32 else (20, 20)}
+    tiles = {s: 3 * -(-63 // x) * -(-63 // y) for s, (x, y) in cells.items()}
+    own = {0: tiles[0]}
+    assert common_shape(lib, fp32, own, tiles) in (6, 7, 8)
+    slow = {s: 3.0 for s in (6, 7, 8, 9)}
+    assert common_shape(lib, fp32, own, tiles, slow, 0.5) == -1
+    assert common_shape(lib, fp32, own, tiles, {6: 3.0, 7: 0.1, 8: 3.0, 9: 3.0}) == 7
+    assert common_shape(lib, fp32, own, tiles, own_scale=0.0) == -1

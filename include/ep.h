@@ -379,7 +379,8 @@ int ep_batch_init(int n, const ep_params* p, const double* const* cohesion, void
  * get a second shape per size for their FP64 finishing sweeps, tuned the
  * same way.  While few models are left, the batch still uses shapes for few
  * tiles, where the tuner's times of those, scaled to what is left, are
- * shorter.  The timed sweeps leave the state unchanged.  Optional; the
+ * shorter; with n_check = 2, where every launch does one sweep, it uses
+ * shapes for that.  The timed sweeps leave the state unchanged.  Optional; the
  * default shape is 64 x 8. */
 int ep_batch_tune(ep_batch* b, int reps);
 

@@ -46,13 +46,13 @@ struct ep_batch {
     double* cols;                       // n x 4
     SweepArgs<double>* tab64;           // 2 x n (parity of the ping-pong buffers)
     SweepArgs<float>* tab32;
-    TileRef* list[2][BATCH_SHAPES];     // [precision: 0 FP64, 1 FP32][shape]
-    int* cnt;                           // 2 x BATCH_SHAPES
-    int grid[2][BATCH_SHAPES];
+    TileRef* list[2][ALL_SHAPES];     // [precision: 0 FP64, 1 FP32][shape]
+    int* cnt;                           // 2 x ALL_SHAPES
+    int grid[2][ALL_SHAPES];
     std::vector<SweepArgs<double>> h_tab64;
     std::vector<SweepArgs<float>> h_tab32;
-    std::vector<TileRef> h_list[2][BATCH_SHAPES];
-    int h_cnt[2 * BATCH_SHAPES];
+    std::vector<TileRef> h_list[2][ALL_SHAPES];
+    int h_cnt[2 * ALL_SHAPES];
     std::vector<unsigned long long> h_red;
     std::vector<double> h_cols;
     double cs32, cs64;                  // cell-sweeps of the current replay set-up
@@ -106,7 +106,7 @@ int validate_batch(int n, const ep_params* p)
 // Layout of the batch workspace: the models, then the batch arrays.
 struct BatchLayout {
     std::vector<size_t> model_off;
-    size_t red, cols, tab64, tab32, lists[2][BATCH_SHAPES], cnt, total;
+    size_t red, cols, tab64, tab32, lists[2][ALL_SHAPES], cnt, total;
 };
 
 BatchLayout layout(int n, const ep_params* p)
@@ -124,13 +124,13 @@ BatchLayout layout(int n, const ep_params* p)
     L.tab32 = take((size_t)3 * n * sizeof(SweepArgs<float>));
     const bool fp32 = p[0].precision == EP_FP32_FIELDS;
     for (int q = 0; q < 2; ++q)
-        for (int s = 0; s < BATCH_SHAPES; ++s) {
+        for (int s = 0; s < ALL_SHAPES; ++s) {
             long c = 0;
             if (q == 0 || fp32)
                 for (int i = 0; i < n; ++i) c += tiles2d(q == 1, s, p[i].nx, p[i].ny);
             L.lists[q][s] = take((size_t)std::max(c, 1L) * sizeof(TileRef));
         }
-    L.cnt = take(2 * BATCH_SHAPES * sizeof(int));
+    L.cnt = take(2 * ALL_SHAPES * sizeof(int));
     L.total = off;
     return L;
 }
@@ -164,24 +164,25 @@ int own_shape(const ep_batch* b, int i, int q) { return (q == 1 || !b->fp32) ? b
 template <typename F>
 void count_tiles(const ep_batch* b, int q, F active, long* own, long* tiles)
 {
-    std::fill(own, own + BATCH_SHAPES, 0L);
-    std::fill(tiles, tiles + BATCH_SHAPES, 0L);
+    std::fill(own, own + ALL_SHAPES, 0L);
+    std::fill(tiles, tiles + ALL_SHAPES, 0L);
     for (int i = 0; i < b->n; ++i) {
         if (!active(i, q)) continue;
         const ep_handle* h = b->m[i];
         own[own_shape(b, i, q)] += tiles2d(q == 1, own_shape(b, i, q), h->nx, h->ny);
-        for (int s = 0; s < BATCH_SHAPES; ++s) tiles[s] += tiles2d(q == 1, s, h->nx, h->ny);
+        for (int s = 0; s < ALL_SHAPES; ++s) tiles[s] += tiles2d(q == 1, s, h->nx, h->ny);
     }
 }
 
 // Tile lists of the running models (precision of each model's current
 // sweeps), or of all models when all_models is set, in FP32 when all32 (the
 // batch precision) else in FP64.  Running models of a precision take their
-// (tuned) shapes, or together one of the others (tile2d_common).
+// (tuned) shapes, or together one of the others (tile2d_common; checks every
+// two sweeps: tile2d_one_sweep).
 void fill_lists(ep_batch* b, bool all_models, bool all32 = true)
 {
     for (int q = 0; q < 2; ++q)
-        for (int s = 0; s < BATCH_SHAPES; ++s) b->h_list[q][s].clear();
+        for (int s = 0; s < ALL_SHAPES; ++s) b->h_list[q][s].clear();
     b->cs32 = b->cs64 = 0;
     auto active = [&](int i, int q) {
         if (all_models) return (b->fp32 && all32) == (q == 1);
@@ -190,9 +191,11 @@ void fill_lists(ep_batch* b, bool all_models, bool all32 = true)
     for (int q = 0; q < 2; ++q) {
         int common = -1;
         if (!all_models) {
-            long own[BATCH_SHAPES], tiles[BATCH_SHAPES];
+            long own[ALL_SHAPES], tiles[ALL_SHAPES];
             count_tiles(b, q, active, own, tiles);
-            common = tile2d_common(q == 1, own, tiles, b->scale[q], b->own_scale[q], b->ncu);
+            common = b->n_check == 2       // one sweep per launch of a replay
+                         ? tile2d_one_sweep(q == 1, tiles[ONE_SWEEP], tiles[ONE_SWEEP + 1], b->ncu)
+                         : tile2d_common(q == 1, own, tiles, b->scale[q], b->own_scale[q], b->ncu);
         }
         for (int i = 0; i < b->n; ++i) {
             if (!active(i, q)) continue;
@@ -207,7 +210,7 @@ void fill_lists(ep_batch* b, bool all_models, bool all32 = true)
         }
     }
     for (int q = 0; q < 2; ++q)
-        for (int s = 0; s < BATCH_SHAPES; ++s) b->h_cnt[q * BATCH_SHAPES + s] = (int)b->h_list[q][s].size();
+        for (int s = 0; s < ALL_SHAPES; ++s) b->h_cnt[q * ALL_SHAPES + s] = (int)b->h_list[q][s].size();
 }
 
 int upload(ep_batch* b)
@@ -218,7 +221,7 @@ int upload(ep_batch* b)
         BCHK(b, hipMemcpyAsync(b->tab32, b->h_tab32.data(), n2 * sizeof(SweepArgs<float>), hipMemcpyHostToDevice,
                                b->st));
     for (int q = 0; q < 2; ++q)
-        for (int s = 0; s < BATCH_SHAPES; ++s)
+        for (int s = 0; s < ALL_SHAPES; ++s)
             if (!b->h_list[q][s].empty())
                 BCHK(b, hipMemcpyAsync(b->list[q][s], b->h_list[q][s].data(), b->h_list[q][s].size() * sizeof(TileRef),
                                        hipMemcpyHostToDevice, b->st));
@@ -228,13 +231,13 @@ int upload(ep_batch* b)
     return EP_OK;
 }
 
-// Bit q * BATCH_SHAPES + shape for every non-empty tile list (q: 0 FP64, 1 FP32).
+// Bit q * ALL_SHAPES + shape for every non-empty tile list (q: 0 FP64, 1 FP32).
 unsigned list_mask(const ep_batch* b)
 {
     unsigned m = 0;
     for (int q = 0; q < 2; ++q)
-        for (int sh = 0; sh < BATCH_SHAPES; ++sh)
-            if (b->h_cnt[q * BATCH_SHAPES + sh] > 0) m |= 1u << (q * BATCH_SHAPES + sh);
+        for (int sh = 0; sh < ALL_SHAPES; ++sh)
+            if (b->h_cnt[q * ALL_SHAPES + sh] > 0) m |= 1u << (q * ALL_SHAPES + sh);
     return m;
 }
 
@@ -248,8 +251,8 @@ void enqueue_sweeps(ep_batch* b, int nsw, bool check, bool reset, bool alternate
 {
     if (reset) launch_reset_red_n(b->red, b->n, s);
     for (int q = 1; q >= 0; --q)
-        for (int sh = 0; sh < BATCH_SHAPES; ++sh) {
-            if (!(mask >> (q * BATCH_SHAPES + sh) & 1u)) continue;
+        for (int sh = 0; sh < ALL_SHAPES; ++sh) {
+            if (!(mask >> (q * ALL_SHAPES + sh) & 1u)) continue;
             const int k = kTiles2d[q][sh].k;
             int n = (nsw + k - 1) / k;
             if (alternate && n % 2 != 0) ++n;
@@ -261,7 +264,7 @@ void enqueue_sweeps(ep_batch* b, int nsw, bool check, bool reset, bool alternate
                 l.ns = nsw / n + (c < nsw % n ? 1 : 0);
                 l.mode = (check && c == n - 1) ? MODE_CHECK : MODE_UPDATE;
                 const int slot = !alternate ? 1 : c == 0 ? 0 : (c & 1) ? 2 : 1;
-                const int* cnt = b->cnt + q * BATCH_SHAPES + sh;
+                const int* cnt = b->cnt + q * ALL_SHAPES + sh;
                 if (q == 1) launch_sweep_batch_2d<float>(b->tab32 + slot * b->n, b->list[1][sh], cnt, l, s);
                 else launch_sweep_batch_2d<double>(b->tab64 + slot * b->n, b->list[0][sh], cnt, l, s);
             }
@@ -373,7 +376,7 @@ int ep_batch_init(int n, const ep_params* p, const double* const* cohesion, void
     b->tab64 = (SweepArgs<double>*)(base + L.tab64);
     b->tab32 = (SweepArgs<float>*)(base + L.tab32);
     for (int q = 0; q < 2; ++q)
-        for (int s = 0; s < BATCH_SHAPES; ++s) b->list[q][s] = (TileRef*)(base + L.lists[q][s]);
+        for (int s = 0; s < ALL_SHAPES; ++s) b->list[q][s] = (TileRef*)(base + L.lists[q][s]);
     b->cnt = (int*)(base + L.cnt);
     if (hipMemsetAsync(base + L.red, 0, L.total - L.red, b->st) != hipSuccess) return fail(EP_EDEVICE);
     for (int i = 0; i < n; ++i) {
@@ -396,7 +399,7 @@ int ep_batch_init(int n, const ep_params* p, const double* const* cohesion, void
         std::fill(b->scale[q], b->scale[q] + BATCH_SHAPES, 1.0);
         b->own_scale[q] = 1.0;
     }
-    for (int s = 0; s < BATCH_SHAPES; ++s) {
+    for (int s = 0; s < ALL_SHAPES; ++s) {
         b->grid[0][s] = ncu * std::min(8, batch_blocks_per_cu<double>(s));
         b->grid[1][s] = ncu * std::min(8, batch_blocks_per_cu<float>(s));
     }
@@ -486,7 +489,7 @@ int ep_batch_tune(ep_batch* b, int reps)
         // the tuned shapes and those for few tiles against their modelled times
         const int q = b->fp32 && all32 ? 1 : 0;
         const auto all = [](int, int) { return true; };
-        long own[BATCH_SHAPES], tiles[BATCH_SHAPES];
+        long own[ALL_SHAPES], tiles[ALL_SHAPES];
         count_tiles(b, q, all, own, tiles);
         double model = 0;
         for (int s = 0; s < BATCH_SHAPES; ++s)

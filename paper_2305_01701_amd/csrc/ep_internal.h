@@ -100,7 +100,8 @@ struct Tile2d {
 // the shapes with two and with three sweeps.
 int tuned_sweeps(int reps);
 constexpr int ONE_SWEEP = BATCH_SHAPES;           // two more for launches of one sweep: 60 x 12 cells, 60 x 28
-extern const Tile2d kTiles2d[2][BATCH_SHAPES + 2];   // [FP64, FP32]
+constexpr int ALL_SHAPES = BATCH_SHAPES + 2;
+extern const Tile2d kTiles2d[2][ALL_SHAPES];      // [FP64, FP32]
 inline long tiles2d(bool fp32, int shape, int nx, int ny)
 {
     const Tile2d& t = kTiles2d[fp32][shape];
@@ -114,8 +115,13 @@ int tile2d_choice(bool fp32, int nx, int ny, int cus);
 // together (tiles[s] tiles with shape s), or -1: their own (own[s] tiles).
 // scale: measured over modelled time of each shape, own_scale: of their own.
 int tile2d_common(bool fp32, const long* own, const long* tiles, const double* scale, double own_scale, int cus);
-// Shape of a launch of one sweep of one model.
-int tile2d_one_sweep(bool fp32, int nx, int ny, int cus);
+// Shape of a launch of one sweep with t12 tiles of 60 x 12 cells or t28 of
+// 60 x 28, and that of one model.
+int tile2d_one_sweep(bool fp32, long t12, long t28, int cus);
+inline int tile2d_one_sweep(bool fp32, int nx, int ny, int cus)
+{
+    return tile2d_one_sweep(fp32, tiles2d(fp32, ONE_SWEEP, nx, ny), tiles2d(fp32, ONE_SWEEP + 1, nx, ny), cus);
+}
 
 struct Launch2d {
     int shape, mode, ns;   // ns <= K sweeps (MODE_PHYS: a shape of one sweep); the last one reduces when mode is MODE_CHECK

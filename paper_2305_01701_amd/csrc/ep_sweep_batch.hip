@@ -92,7 +92,7 @@ int occupancy()
 // What a launch with a shape costs, in us: alone with at most one workgroup
 // per CU (t1), else t0 + t2 per workgroup on a CU; measured on 18 grids from
 // 31^2 to 2047^2 (not of the shapes of one sweep: tile2d_one_sweep).
-const Tile2d kTiles2d[2][BATCH_SHAPES + 2] = {
+const Tile2d kTiles2d[2][ALL_SHAPES] = {
     {{56, 8, 2, 64, 8, 10.5, 4.5, 5.7}, {56, 8, 2, 64, 4, 13.0, 7.0, 5.6}, {24, 24, 2, 32, 8, 15.0, 8.0, 6.0},
      {120, 8, 2, 128, 4, 16.0, 3.0, 13.0}, {52, 20, 3, 64, 16, 20.5, 1.0, 20.5}, {24, 24, 2, 32, 16, 11.0, 4.5, 6.2},
      {12, 12, 5, 32, 32, 15.8, 1.8, 14.0}, {16, 16, 4, 32, 32, 14.0, 2.0, 12.3}, {20, 20, 3, 32, 32, 12.0, 1.5, 10.7},
@@ -158,9 +158,8 @@ int tile2d_common(bool fp32, const long* own, const long* tiles, const double* s
 // time, rounds: 17 us one of 60 x 28, 12 us one of 60 x 12 (1500^2: 62 and 75
 // us; 2047^2: 132 and 111).  In FP64 the larger tiles never gain there (1023^2:
 // 66 and 62.5 us).
-int tile2d_one_sweep(bool fp32, int nx, int ny, int cus)
+int tile2d_one_sweep(bool fp32, long t12, long t28, int cus)
 {
-    const long t12 = tiles2d(fp32, ONE_SWEEP, nx, ny), t28 = tiles2d(fp32, ONE_SWEEP + 1, nx, ny);
     auto rounds = [&](long tiles, long per_cu) { return (tiles + per_cu * cus - 1) / (per_cu * cus); };
     const bool large = (t28 <= cus && t12 > cus) || (fp32 && 17 * rounds(t28, 2) < 12 * rounds(t12, 3));
     return ONE_SWEEP + large;

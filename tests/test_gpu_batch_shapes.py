@@ -45,3 +45,29 @@ def test_every_shape_gives_the_same_bits(prec):
         for i in range(3):
             for k in fr[i]:
                 assert np.array_equal(f[i][k], fr[i][k]), (shape, i, k)
+
+
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp64", "fp32"])
+def test_checks_every_two_sweeps_equal_single_models(prec):
+    """n_check = 2: launches of one sweep, on their own tiles."""
+    from gpu_common import solver
+    from paper_2305_01701_amd import ep
+    ms = [m.with_(n_check=2, max_iter=60) for m in models()] + [Model(ndim=2, nx=700, ny=500, n_check=2, max_iter=60)]
+    b = ep.Batch(ms, precision=prec)
+    names = IT2 + ["p_old"]
+    r = np.random.Generator(np.random.PCG64(9))
+    alone = []
+    for i, m in enumerate(ms):
+        g = solver(m, precision=prec)
+        v = g.get("vx") + 1e-3 * r.standard_normal(g.size("vx"))
+        g.set("vx", v)
+        b.model(i).set("vx", v)
+        alone.append((g, g.load_step(), g.history()[0]))
+    st = b.load_step()
+    for i, (g, s, hist) in enumerate(alone):
+        say("n_check 2", prec, i, st[i]["iters"], s["iters"])
+        assert st[i]["iters"] == s["iters"] and np.array_equal(b.model(i).history()[0], hist)
+        for k in names:
+            assert np.array_equal(b.model(i).get(k), g.get(k)), (i, k)
+        g.close()
+    b.close()

@@ -53,9 +53,10 @@ def test_planes_beyond_2_gib_are_out_of_range(lib):
 
 
 def one_sweep(lib, fp32, nx, ny):
-    f = lib._ZN2ep16tile2d_one_sweepEbiii
+    f = lib._ZN2ep16tile2d_one_sweepEblli
     f.restype = C.c_int
-    return f(C.c_bool(fp32), nx, ny, 256)
+    tiles = lambda y: C.c_long(-(-nx // 60) * -(-ny // y))
+    return f(C.c_bool(fp32), tiles(12), tiles(28), 256)
 
 
 def test_single_2d_sweeps_take_tiles_without_a_wide_halo(lib):

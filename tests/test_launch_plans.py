@@ -10,6 +10,7 @@ WIDE, SQUARE, SMALL = 0, 1, 2      # tiles of the fused 3D sweep: 64 x 11, 32 x 
 
 @pytest.fixture(scope="module")
 def lib():
+    import torch  # noqa: F401  (its HIP runtime, before the library binds to another)
     from paper_2305_01701_amd import ep
     if not os.path.exists(ep.LIB_PATH):
         from paper_2305_01701_amd import build

@@ -94,6 +94,7 @@ constexpr int TUNED_SHAPES = 6;                   // ... of which the autotuner 
 struct Tile2d {
     int tx, ty, k;         // cells a workgroup owns, sweeps per launch at most
     int pass_x, pass_y;    // points one pass of its threads covers (the shape's name)
+    bool single;           // single models choose it (else only batches, which have no per-cell G)
     double t1, t0, t2;     // cost of a launch (tile2d_cost)
 };
 // Sweeps that the autotuner times for `reps` requested ones: whole launches of

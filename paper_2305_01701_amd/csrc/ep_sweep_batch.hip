@@ -42,17 +42,29 @@ void k_batch_2d(const SweepArgs<R>* __restrict__ table, const TileRef* __restric
 }
 
 // Tile shapes of each precision: index, TX, TY, K, threads, waves per SIMD to
-// fit in registers.  The first six are the tuner's, named by the points that
+// fit in registers, whether single models choose it (and it has a form with a
+// per-cell G), and what a launch costs, in us: alone with at most one
+// workgroup per CU (t1), else t0 + t2 per workgroup on a CU; measured on 18
+// grids from 31^2 to 2047^2 (not for the shapes of one sweep:
+// tile2d_one_sweep).  The first six are the tuner's, named by the points that
 // one pass of the workgroup's threads covers (64 x 8, 64 x 4, 32 x 8, 128 x 4,
 // 64 x 16, 32 x 16), the last two those of launches of one sweep.
-#define EP_TILES_32(X) X(0, 52, 20, 3, 512, 6) X(1, 56, 8, 2, 256, 5) X(2, 24, 24, 2, 256, 5) X(3, 120, 8, 2, 512, 5) \
-    X(4, 52, 20, 3, 1024, 8) X(5, 24, 24, 2, 512, 8) X(6, 12, 12, 5, 1024, 8) X(7, 16, 16, 4, 1024, 8)              \
-    X(8, 20, 20, 3, 1024, 8) X(9, 32, 32, 4, 768, 6) X(10, 60, 12, 1, 512, 6) X(11, 60, 28, 1, 1024, 8)
-#define EP_TILES_64(X) X(0, 56, 8, 2, 512, 4) X(1, 56, 8, 2, 256, 3) X(2, 24, 24, 2, 256, 3) X(3, 120, 8, 2, 512, 2) \
-    X(4, 52, 20, 3, 1024, 4) X(5, 24, 24, 2, 512, 4) X(6, 12, 12, 5, 1024, 4) X(7, 16, 16, 4, 1024, 4)              \
-    X(8, 20, 20, 3, 1024, 4) X(9, 20, 20, 3, 512, 4) X(10, 60, 12, 1, 512, 4) X(11, 60, 28, 1, 1024, 4)
+#define EP_TILES_32(X)                                                                                                 \
+    X(0, 52, 20, 3, 512, 6, false, 15.7, 5.0, 7.0) X(1, 56, 8, 2, 256, 5, true, 10.0, 2.0, 2.6)                        \
+    X(2, 24, 24, 2, 256, 5, false, 10.0, 2.0, 3.5) X(3, 120, 8, 2, 512, 5, false, 11.0, 2.0, 6.4)                      \
+    X(4, 52, 20, 3, 1024, 8, true, 11.2, 3.0, 6.9) X(5, 24, 24, 2, 512, 8, true, 8.0, 1.5, 3.2)                        \
+    X(6, 12, 12, 5, 1024, 8, true, 9.6, 1.7, 5.9) X(7, 16, 16, 4, 1024, 8, true, 8.5, 1.6, 4.9)                        \
+    X(8, 20, 20, 3, 1024, 8, true, 7.4, 2.3, 3.9) X(9, 32, 32, 4, 768, 6, true, 17.0, 2.5, 10.2)                       \
+    X(10, 60, 12, 1, 512, 6, true, 0, 0, 0) X(11, 60, 28, 1, 1024, 8, true, 0, 0, 0)
+#define EP_TILES_64(X)                                                                                                 \
+    X(0, 56, 8, 2, 512, 4, true, 10.5, 4.5, 5.7) X(1, 56, 8, 2, 256, 3, false, 13.0, 7.0, 5.6)                         \
+    X(2, 24, 24, 2, 256, 3, true, 15.0, 8.0, 6.0) X(3, 120, 8, 2, 512, 2, true, 16.0, 3.0, 13.0)                       \
+    X(4, 52, 20, 3, 1024, 4, true, 20.5, 1.0, 20.5) X(5, 24, 24, 2, 512, 4, true, 11.0, 4.5, 6.2)                      \
+    X(6, 12, 12, 5, 1024, 4, true, 15.8, 1.8, 14.0) X(7, 16, 16, 4, 1024, 4, true, 14.0, 2.0, 12.3)                    \
+    X(8, 20, 20, 3, 1024, 4, true, 12.0, 1.5, 10.7) X(9, 20, 20, 3, 512, 4, true, 13.7, 5.0, 7.6)                      \
+    X(10, 60, 12, 1, 512, 4, true, 0, 0, 0) X(11, 60, 28, 1, 1024, 4, true, 0, 0, 0)
 
-template <typename R, int TX, int TY, int K, int NT, int E>
+template <typename R, int TX, int TY, int K, int NT, int E, bool SINGLE>
 void run(const SweepArgs<R>* table, const TileRef* list, const int* count, const Launch2d& l, hipStream_t s)
 {
     const int grid = l.grid > 0 ? l.grid : 1;
@@ -66,12 +78,16 @@ void run(const SweepArgs<R>* table, const TileRef* list, const int* count, const
             return;
         }
     }
-    if (l.has_g) {
-        if (l.mode == MODE_CHECK)
-            k_batch_2d<R, TX, TY, K, MODE_CHECK, NT, E, true><<<grid, NT, 0, s>>>(table, list, count, l.tiles, l.nbx, l.ns);
-        else
-            k_batch_2d<R, TX, TY, K, MODE_UPDATE, NT, E, true><<<grid, NT, 0, s>>>(table, list, count, l.tiles, l.nbx, l.ns);
-    } else if (l.mode == MODE_CHECK)
+    if constexpr (SINGLE) {
+        if (l.has_g) {
+            if (l.mode == MODE_CHECK)
+                k_batch_2d<R, TX, TY, K, MODE_CHECK, NT, E, true><<<grid, NT, 0, s>>>(table, list, count, l.tiles, l.nbx, l.ns);
+            else
+                k_batch_2d<R, TX, TY, K, MODE_UPDATE, NT, E, true><<<grid, NT, 0, s>>>(table, list, count, l.tiles, l.nbx, l.ns);
+            return;
+        }
+    }
+    if (l.mode == MODE_CHECK)
         k_batch_2d<R, TX, TY, K, MODE_CHECK, NT, E, false><<<grid, NT, 0, s>>>(table, list, count, l.tiles, l.nbx, l.ns);
     else
         k_batch_2d<R, TX, TY, K, MODE_UPDATE, NT, E, false><<<grid, NT, 0, s>>>(table, list, count, l.tiles, l.nbx, l.ns);
@@ -89,18 +105,18 @@ int occupancy()
 
 }  // namespace
 
-// What a launch with a shape costs, in us: alone with at most one workgroup
-// per CU (t1), else t0 + t2 per workgroup on a CU; measured on 18 grids from
-// 31^2 to 2047^2 (not of the shapes of one sweep: tile2d_one_sweep).
-const Tile2d kTiles2d[2][ALL_SHAPES] = {
-    {{56, 8, 2, 64, 8, 10.5, 4.5, 5.7}, {56, 8, 2, 64, 4, 13.0, 7.0, 5.6}, {24, 24, 2, 32, 8, 15.0, 8.0, 6.0},
-     {120, 8, 2, 128, 4, 16.0, 3.0, 13.0}, {52, 20, 3, 64, 16, 20.5, 1.0, 20.5}, {24, 24, 2, 32, 16, 11.0, 4.5, 6.2},
-     {12, 12, 5, 32, 32, 15.8, 1.8, 14.0}, {16, 16, 4, 32, 32, 14.0, 2.0, 12.3}, {20, 20, 3, 32, 32, 12.0, 1.5, 10.7},
-     {20, 20, 3, 32, 16, 13.7, 5.0, 7.6}, {60, 12, 1, 64, 8, 0, 0, 0}, {60, 28, 1, 64, 16, 0, 0, 0}},
-    {{52, 20, 3, 64, 8, 15.7, 5.0, 7.0}, {56, 8, 2, 64, 4, 10.0, 2.0, 2.6}, {24, 24, 2, 32, 8, 10.0, 2.0, 3.5},
-     {120, 8, 2, 128, 4, 11.0, 2.0, 6.4}, {52, 20, 3, 64, 16, 11.2, 3.0, 6.9}, {24, 24, 2, 32, 16, 8.0, 1.5, 3.2},
-     {12, 12, 5, 32, 32, 9.6, 1.7, 5.9}, {16, 16, 4, 32, 32, 8.5, 1.6, 4.9}, {20, 20, 3, 32, 32, 7.4, 2.3, 3.9},
-     {32, 32, 4, 48, 16, 17.0, 2.5, 10.2}, {60, 12, 1, 64, 8, 0, 0, 0}, {60, 28, 1, 64, 16, 0, 0, 0}}};
+#define X(i, TX, TY, K, NT, E, SINGLE, t1, t0, t2) {TX, TY, K, TX + 4 * K, NT / (TX + 4 * K), SINGLE, t1, t0, t2},
+const Tile2d kTiles2d[2][ALL_SHAPES] = {{EP_TILES_64(X)}, {EP_TILES_32(X)}};
+#undef X
+#define X(i, ...) i,
+constexpr bool in_order(const int (&at)[ALL_SHAPES])
+{
+    for (int s = 0; s < ALL_SHAPES; ++s)
+        if (at[s] != s) return false;
+    return true;
+}
+static_assert(in_order({EP_TILES_64(X)}) && in_order({EP_TILES_32(X)}), "the indexes are the places in kTiles2d");
+#undef X
 
 double tile2d_cost(bool fp32, int shape, long tiles, int cus)
 {
@@ -109,7 +125,9 @@ double tile2d_cost(bool fp32, int shape, long tiles, int cus)
     return std::fmax(t.t1, t.t0 + t.t2 * m) / t.k;
 }
 
-// The shape of least modelled time for a model of nx x ny cells.  A launch of
+// The shape of least modelled time for a model of nx x ny cells, of those that
+// are marked for single models (the others only ever gain 2 % on strips of
+// less than 9 cells).  A launch of
 // K sweeps is worth more redundant points the fewer workgroups a grid fills:
 // 12 x 12 tiles with K = 5 up to 16 tiles a side (63^2 FP32 1.9 us per sweep,
 // one sweep per launch of 64 x 16 tiles 5; FP64 3.1 against 7.5), then 16 x 16,
@@ -121,7 +139,7 @@ int tile2d_choice(bool fp32, int nx, int ny, int cus)
     double t_best = INFINITY;
     for (int s = 0; s < BATCH_SHAPES; ++s) {
         const double t = tile2d_cost(fp32, s, tiles2d(fp32, s, nx, ny), cus);
-        if (t < t_best) {
+        if (kTiles2d[fp32][s].single && t < t_best) {
             t_best = t;
             best = s;
         }
@@ -169,7 +187,7 @@ template <typename R>
 void launch_sweep_batch_2d(const SweepArgs<R>* table, const TileRef* list, const int* count, const Launch2d& l,
                            hipStream_t s)
 {
-#define X(i, TX, TY, K, NT, E) case i: run<R, TX, TY, K, NT, E>(table, list, count, l, s); break;
+#define X(i, TX, TY, K, NT, E, SINGLE, ...) case i: run<R, TX, TY, K, NT, E, SINGLE>(table, list, count, l, s); break;
     if constexpr (sizeof(R) == 8) {
         switch (l.shape) { EP_TILES_64(X) }
     } else {
@@ -181,7 +199,7 @@ void launch_sweep_batch_2d(const SweepArgs<R>* table, const TileRef* list, const
 template <typename R>
 int batch_blocks_per_cu(int shape)
 {
-#define X(i, TX, TY, K, NT, E) case i: return occupancy<R, TX, TY, K, NT, E>();
+#define X(i, TX, TY, K, NT, E, ...) case i: return occupancy<R, TX, TY, K, NT, E>();
     if constexpr (sizeof(R) == 8) {
         switch (shape) { EP_TILES_64(X) }
     } else {

@@ -580,9 +580,16 @@ struct TileCost {
     int tile, x, y, res;
     double alone, full, launch;
 };
-const TileCost kCost32[] = {{TILE_WIDE, 64, 11, 2, 3.5, 6.0, 5.0}, {TILE_SQUARE, 32, 16, 2, 2.61, 5.23, 5.0},
-                            {TILE_SMALL, 16, 8, 8, 1.5, 5.8, 2.0}};
-const TileCost kCost64[] = {{TILE_SQUARE, 32, 16, 1, 3.0, 3.3, 5.0}, {TILE_SMALL, 16, 8, 4, 1.9, 4.2, 2.0}};
+template <typename T>
+constexpr TileCost cost_of(int tile, int res, double alone, double full, double launch)
+{
+    return {tile, T::X, T::Y, res, alone, full, launch};
+}
+const TileCost kCost32[] = {cost_of<TileF_wide>(TILE_WIDE, 2, 3.5, 6.0, 5.0),
+                            cost_of<TileF_square>(TILE_SQUARE, 2, 2.61, 5.23, 5.0),
+                            cost_of<TileF_small>(TILE_SMALL, 8, 1.5, 5.8, 2.0)};
+const TileCost kCost64[] = {cost_of<TileD_square>(TILE_SQUARE, 1, 3.0, 3.3, 5.0),
+                            cost_of<TileD_small>(TILE_SMALL, 4, 1.9, 4.2, 2.0)};
 
 }  // namespace
 

@@ -271,13 +271,12 @@ int ep_residual(ep_handle* h, ep_residual_info* r);
 /* Allocation-free variant of ep_residual, for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops, harnesses
  * that forbid hipMalloc).  Same norms as ep_residual, computed by the same
- * kernels; the reduction counters, the two sweep-argument tables and (2D
- * models) the tile list are staged in a static device array of the library
- * (64 KiB per GPU, held until the process ends) instead of the handle's
- * workspace.  Calls no hipMalloc, hipFree or allocating routine; like
+ * kernels; the reduction counters and the two sweep-argument tables are
+ * staged in a static device array of the library (64 KiB per GPU, held until
+ * the process ends) instead of the handle's workspace.  Calls no hipMalloc, hipFree or allocating routine; like
  * ep_residual it writes the handle's second iteration buffer (the state is
- * unchanged).  EP_EINVAL (message in ep_last_error) for a 2D model whose tile
- * list exceeds the array (more than 8,000 tiles of 64 x 16 cells).  The
+ * unchanged).  EP_EINVAL (message in ep_last_error) for a 2D model of more
+ * than 8,000 tiles of 64 x 16 cells, whatever tiles its sweeps run on.  The
  * array is shared by every call on the same GPU: calls that overlap on one
  * GPU (other streams or threads) race and must be serialised by the caller.
  * Synchronous. */
@@ -356,7 +355,8 @@ int ep_sweep_timing(const ep_handle* h, int precision, double* avg_ms, long* swe
  * FP32 hand-over.  Per model, the iterates, iteration counts and statistics
  * are those of ep_load_step on that model alone.
  * Requirements: every model 2D, all with the same precision and the same
- * (resolved) n_check, which must be even; at most 32767 tiles per direction.
+ * (resolved) n_check, which must be even; nx at most 32767 * 32 and ny at
+ * most 32767 * 4 cells.
  * Memory: one caller-owned workspace of ep_batch_workspace_size() bytes
  * (256-byte aligned), as for ep_init.  Stream: as for ep_init; graph
  * replays are launched on it (a private stream is used only to record the
@@ -384,10 +384,10 @@ int ep_batch_init(int n, const ep_params* p, const double* const* cohesion, void
  * default shape is 64 x 8. */
 int ep_batch_tune(ep_batch* b, int reps);
 
-/* Tile shape of model i: the points that one pass of a workgroup's threads
- * covers.  A workgroup makes several passes over its tile and its halo and
- * several sweeps per launch; while few models are left, the batch uses
- * shapes for few tiles instead. */
+/* Tile shape of model i, as a name: the points that one pass of a workgroup's
+ * threads covers.  The tile itself is smaller or larger: a workgroup makes
+ * several passes over it and its halo, and several sweeps per launch.  Where
+ * other shapes run instead: ep_batch_tune. */
 int ep_batch_tile_shape(const ep_batch* b, int i, int* tx, int* ty);
 
 /* One load increment of every model; st: n entries (required), filled as by

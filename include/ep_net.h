@@ -52,8 +52,9 @@ typedef struct ep_net_config {
                                 network (no sample slots, no activation gradients: about half
                                 the workspace); ep_net_train and ep_net_gradient then fail.
                                 A training network (> 0) also holds a buffer of partial
-                                gradient sums, added in a fixed order: its gradients and training
-                                runs repeat bit for bit */
+                                gradient sums (by the grid, up to 357 MB with 32 channels and 282
+                                with 16), added in a fixed order: its gradients and training runs
+                                repeat bit for bit */
     float scale[4];          /* stress, plastic strain, input velocity change, output velocity change (> 0) */
     int   seed;              /* weight initialisation: He-normal, zero head */
 } ep_net_config;

@@ -948,15 +948,16 @@ void handle_free(ep_handle* h)
 
 // ---- allocation-free residual: the static device scratch ------------------
 // File-scope device array that ep_residual_noalloc stages its reduction
-// counters, sweep-argument tables and 2D tile list in (each GPU the library
-// runs on holds one copy until the process ends).  Host code reaches it only
+// counters and sweep-argument tables in (each GPU the library runs on holds
+// one copy until the process ends).  Host code reaches it only
 // through the address hipGetSymbolAddress returns for the current device.
 constexpr size_t NOALLOC_SCRATCH_BYTES = 64 * 1024;
 static __device__ __align__(256) unsigned char scratch[NOALLOC_SCRATCH_BYTES];
 
 // Layout: reduction counters, then two FP64 argument tables (PT and physical
 // evaluation).  2D models of more than 8,000 tiles of 64 x 16 cells are
-// refused (the interface's stated limit).
+// refused: the interface's stated limit, from when a list of those tiles was
+// staged here as well.
 constexpr size_t NA_RED = 0;
 constexpr size_t NA_TAB = 256;
 constexpr long NOALLOC_MAX_TILES = 8000;

@@ -5,7 +5,9 @@
 // sy = round_up(nx + 1, 32) and sz = sy * (ny + 1).  Cells use i < nx,
 // x-faces i <= nx, vertices / edges the corresponding "+1" extents, so the
 // neighbour offsets of every staggered field are the same +-1, +-sy, +-sz.
-// Padding entries are never read.
+// Padding up to index nx, ny, nz of each direction is read where a sweep clamps
+// to it, and may hold anything: what is computed from it has to be dropped by
+// a select, never multiplied away.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

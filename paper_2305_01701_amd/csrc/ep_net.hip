@@ -119,7 +119,7 @@ enum { EPI_RELU = 0,      // Y = max(z, 0)
 
 struct ConvArgs {
     const bf16_t* X;       // input, cin channels (level g, or its parent gx with UP)
-    const bf16_t* Wt;      // weights [cout][27][cin]
+    const bf16_t* Wt;      // weights in the order of weight_at
     const float* bias;     // or nullptr
     void* Y;
     bf16_t* Y2;
@@ -308,7 +308,8 @@ __global__ __launch_bounds__(256, 2) void k_conv(ConvArgs a)
     using Frag = std::conditional_t<KC == 32, b8, s4>;       // KC / 4 channels of a voxel or of an output channel
     constexpr int TASKS = CT_N * NP, PER = (TASKS + 255) / 256;
     const ConvIn<UP, FAR> X{a};
-    typename ConvIn<UP, FAR>::Off from[PER];                                      // LDS piece e of a swizzled row: channels 8 (e ^ (tx / 4)) % 32
+    // LDS piece e of a swizzled row: channels 8 (e ^ (tx / 4)) % 32
+    typename ConvIn<UP, FAR>::Off from[PER];
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
         const int e = threadIdx.x + 256 * u, tv = e / NP;

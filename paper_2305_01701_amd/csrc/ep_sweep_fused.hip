@@ -607,8 +607,11 @@ bool fused_preferred(int, bool) { return true; }
 // workgroups of an XCD drift apart in z and lose the halo lines they share
 // in its L2: FP32 511^3 3.72 ms in chunks of 16 planes, 3.99 in 64) were
 // fitted to sweeps timed on 28 grids from 20^3 to 511^3 with every tile and
-// chunk length: the choice is within 4 % (FP32) and 6 % (FP64) of the best
-// of them, 1 % on average.  FP64 chunks of 64 planes only where a plane has
+// the chunk lengths below.  Over 55 grids and slabs, 72 timings per precision
+// with the per-cell G, the choice is within 0.5 % of the best of any tile and
+// length on average and 10 % (FP32: 100^3 51 us, 46 in chunks of 13) and 12 %
+// (FP64: 190 x 127 x 101 157 us, 141 in chunks of 21) at worst: lengths that
+// divide nz evenly are not all in the list.  FP64 chunks of 64 planes only where a plane has
 // at most 1 MB: 255^3 0.81 against 0.85 ms in chunks of 32, but 511^3 7.75
 // against 6.59 ms in chunks of 43.  The small FP32 tiles read 1.9 values per
 // point, which at 5.1 TB/s takes longer than their march where they fill the

@@ -16,14 +16,15 @@
 //   velocities twice, from L2); the halo reads of neighbouring tiles are
 //   served by L2 (blocks are remapped so that spatial neighbours run on the
 //   same XCD).
-//   What bounds it: large grids the memory traffic (255^3 FP32: 2.7 GB per
-//   sweep with 32 x 16 tiles, 5.4 TB/s), small ones the latency of a march
-//   step.  An earlier form kept every plane twice in LDS, split the points
-//   over the threads once for all stages and loaded behind branches: 80
-//   vector registers with spills, whose reloads waited for the loads of the
-//   next step.  Per sweep, then and now, in us: 255^3 FP32 541 and 464, FP64
-//   989 and 811; 190 x 127 x 101 FP64 247 and 155; 63^3 FP32 142 and 18.5,
-//   FP64 194 and 25 (short chunks included).
+//   What bounds it: large grids the memory traffic (beyond the L2, 255^3 FP32:
+//   2.45 GB per sweep, 1.48 times the algorithmic bytes, at 5.4 TB/s; 511^3
+//   22.7 GB at 6.0), small ones the latency of a march step.  An earlier form
+//   kept every plane twice in LDS, split the points over the threads once for
+//   all stages and loaded behind branches: 80 vector registers with spills,
+//   whose reloads waited for the loads of the next step.  Per sweep, then and
+//   now, in us: 255^3 FP32 541 and 452, FP64 989 and 803; 190 x 127 x 101 FP64
+//   247 and 159; 63^3 FP32 142 and 18.2, FP64 194 and 25.5 (short chunks
+//   included).
 //   2D: the same stages on a single TX x TY tile (ep_tile2d.h, run by the
 //   tile-list kernel of ep_sweep_batch.hip for single models and batches).
 //
